@@ -40,6 +40,8 @@ template <> struct Elem<bf16> {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
+// four consecutive floats in memory (global memory takes 16-byte loads at any 4-byte alignment)
+typedef float floatx4u_t __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
 

@@ -21,7 +21,7 @@
 //  * Epilogues: float32 store, float32 residual add in place, store in the
 //    model dtype, SwiGLU (gate and up strips of the same features sit in the
 //    same wave, so silu(gate) * up is formed in registers).
-// float32 path: a plain LDS-tiled FMA kernel on row-major weights.
+// float32 path: float32 matrix-core products on row-major weights, K split over a workgroup's waves.
 #include <atomic>
 #include <type_traits>
 
@@ -399,46 +399,105 @@ struct GemmF {
   int M, N, K, ldx;
 };
 
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF g) {
-  constexpr int TM = 16, TN = 64, TK = 32;
-  constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
-  __shared__ float As[TM][TK + 1];
-  __shared__ float Bs[NB][TN][TK + 1];
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-  float acc[NB][4] = {};
-  for (int k0 = 0; k0 < g.K; k0 += TK) {
-    for (int e = tid; e < TM * TK; e += 256) {
-      const int r = e / TK, c = e % TK, m = m0 + r;
-      As[r][c] = (m < g.M && k0 + c < g.K) ? g.X[(long)m * g.ldx + k0 + c] : 0.f;
-    }
-    for (int nb = 0; nb < NB; ++nb)
-      for (int e = tid; e < TN * TK; e += 256) {
-        const int r = e / TK, c = e % TK, n = n0 + r;
-        Bs[nb][r][c] = (n < g.N && k0 + c < g.K) ? g.W[((long)nb * g.N + n) * g.K + k0 + c] : 0.f;
-      }
-    __syncthreads();
-    for (int c = 0; c < TK; ++c) {
-      const float x = As[ty][c];
+// float32 products on v_mfma_f32_16x16x4_f32 (float32 multiply-adds throughout).  One
+// workgroup owns an output tile of 16 MT x 16 NT; its KW waves split K between them, and
+// their partial tiles meet in LDS, where they are added in wave order.  A lane loads 16
+// bytes (4 consecutive k) of its row of X and of W, straight from memory into operand
+// registers: lane group g holds k = 16 i + 4 g + q, and product q of the four takes
+// element q of both, so X and W agree on the order of k.
+//  The small decoders this path serves are bound by latency, not by rates: at 4-16 rows and
+// a few hundred columns the launch is a handful of tiles, so what counts is the length of
+// the serial chain in each.  One 16 x 16 tile per workgroup with K split over eight waves
+// gives four times the workgroups and an eighth of the chain of a 16 x 64 tile that stages
+// 32 k at a time through LDS (4 x 256 outputs over K = 1024: 70 us there, 4.5 us here).
+template <int EPI, int MT, int NT, int KW>
+__global__ __launch_bounds__(64 * KW) void gemm_f32_kernel(GemmF g) {
+  constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;   // SwiGLU: the gate columns, then the up columns
+  constexpr int UB = MT * NT == 1 ? 4 : 2;        // k groups of 16 loaded together
+  constexpr int TILE = 256 * MT * NT;
+  __shared__ float sh[KW][NB * TILE];
+  const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, g4 = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = blockIdx.y * 16 * MT, n0 = blockIdx.x * 16 * NT;
+  const int units = g.K / 16;                     // K is a multiple of 64
+  const int u0 = units * w / KW, u1 = units * (w + 1) / KW;
+  const float *xp[MT], *wp[NB * NT];              // rows past the edges re-read the last one (never stored)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+  for (int a = 0; a < MT; ++a) xp[a] = g.X + (long)min(m0 + 16 * a + j, g.M - 1) * g.ldx + 4 * g4;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[nb][q] += x * Bs[nb][tx * 4 + q][c];
+  for (int t = 0; t < NB * NT; ++t)
+    wp[t] = g.W + ((long)(t / NT) * g.N + min(n0 + 16 * (t % NT) + j, g.N - 1)) * g.K + 4 * g4;
+  floatx4_t acc[MT][NB * NT];
+#pragma unroll
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int t = 0; t < NB * NT; ++t) acc[a][t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  auto ld = [](const float *p) { return *reinterpret_cast<const floatx4u_t *>(p); };
+  auto mul = [&](const floatx4u_t (&x)[MT], const floatx4u_t (&v)[NB * NT]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int t = 0; t < NB * NT; ++t)
+          acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[a][q], v[t][q], acc[a][t], 0, 0, 0);
+  };
+  int u = u0;
+  for (; u + UB <= u1; u += UB) {                 // all loads of UB groups issued before the first product
+    floatx4u_t x[UB][MT], v[UB][NB * NT];
+#pragma unroll
+    for (int i = 0; i < UB; ++i) {
+#pragma unroll
+      for (int a = 0; a < MT; ++a) x[i][a] = ld(xp[a] + 16 * (u + i));
+#pragma unroll
+      for (int t = 0; t < NB * NT; ++t) v[i][t] = ld(wp[t] + 16 * (u + i));
     }
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < UB; ++i) mul(x[i], v[i]);
   }
-  const int m = m0 + ty;
-  if (m >= g.M) return;
+  for (; u < u1; ++u) {
+    floatx4u_t x[MT], v[NB * NT];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int n = n0 + tx * 4 + q;
-    if (n >= g.N) continue;
+    for (int a = 0; a < MT; ++a) x[a] = ld(xp[a] + 16 * u);
+#pragma unroll
+    for (int t = 0; t < NB * NT; ++t) v[t] = ld(wp[t] + 16 * u);
+    mul(x, v);
+  }
+  // lane holds C[row 16a + 4 g4 + r][col 16t + j]
+#pragma unroll
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int t = 0; t < NB * NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        sh[w][(t / NT) * TILE + (16 * a + 4 * g4 + r) * 16 * NT + 16 * (t % NT) + j] = acc[a][t][r];
+  __syncthreads();
+  for (int e = tid; e < TILE; e += 64 * KW) {
+    const int m = m0 + e / (16 * NT), n = n0 + e % (16 * NT);
+    if (m >= g.M || n >= g.N) continue;
+    float v[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      v[b] = sh[0][b * TILE + e];
+#pragma unroll
+      for (int i = 1; i < KW; ++i) v[b] += sh[i][b * TILE + e];
+    }
     float *y = g.Y + (long)m * g.ldy + n;
-    if (EPI == EPI_ADD_F32) *y += acc[0][q];
-    else if (EPI == EPI_SWIGLU) *y = silu(acc[0][q]) * acc[NB - 1][q];
-    else *y = acc[0][q];
+    if (EPI == EPI_ADD_F32) *y += v[0];
+    else if (EPI == EPI_SWIGLU) *y = silu(v[0]) * v[NB - 1];
+    else *y = v[0];
   }
+}
+
+// 32 x 32 tiles (each loaded operand feeds two products, K split over four waves) where they
+// still give every CU a workgroup, else 16 x 16 tiles and eight waves.
+template <int EPI>
+void launch_f32(const GemmF &g, hipStream_t s) {
+  const long t32 = (long)((g.N + 31) / 32) * ((g.M + 31) / 32);
+  if (t32 >= 256)
+    hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 2, 4>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(256), 0, s, g);
+  else
+    hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, 1, 8>), dim3((g.N + 15) / 16, (g.M + 15) / 16), dim3(512), 0, s, g);
 }
 
 // ------------------------------------------------------------------ LM head, M <= 64
@@ -836,21 +895,19 @@ int launch_gemm(const char *name, int dtype, int epi, int M, int N, int K, const
     return 1;
   } else {
     GemmF g{(const float *)X, (const float *)W, (float *)Y, ldy, M, N, K, ldx};
-    const dim3 grid((N + 63) / 64, (M + 15) / 16), block(256);
     if (epi == EPI_STATS) {     // no fused epilogue on this path: a pass over the output rows
       {
         TraceScope ts(name, s);
-        hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE_F32>, grid, block, 0, s, g);
+        launch_f32<EPI_STORE_F32>(g, s);
       }
       launch_tile_stats((const float *)Y, ldy, M, N, inv_t, plan_lm_head(dtype, M, N, K), tile_stats, s);
       return 1;
     }
     TraceScope ts(name, s);
     switch (epi) {
-      case EPI_STORE_F32: hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE_F32>, grid, block, 0, s, g); break;
-      case EPI_ADD_F32: hipLaunchKernelGGL(gemm_f32_kernel<EPI_ADD_F32>, grid, block, 0, s, g); break;
-      case EPI_STORE_ACT: hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE_ACT>, grid, block, 0, s, g); break;
-      case EPI_SWIGLU: hipLaunchKernelGGL(gemm_f32_kernel<EPI_SWIGLU>, grid, block, 0, s, g); break;
+      case EPI_ADD_F32: launch_f32<EPI_ADD_F32>(g, s); break;
+      case EPI_SWIGLU: launch_f32<EPI_SWIGLU>(g, s); break;
+      default: launch_f32<EPI_STORE_F32>(g, s); break;   // float32 is the model dtype here: both stores are one
     }
   }
   return 1;

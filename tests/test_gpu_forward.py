@@ -68,6 +68,25 @@ def test_tiny_f32_forward(qk_norm):
     assert rel_err(logits, full[:, T0:]) < 1e-4
 
 
+@pytest.mark.parametrize("B,k,vocab,hidden,ffn", [
+    (1, 0, 1000, 256, 1024),      # one row, a vocabulary that ends inside a 16-column tile
+    (3, 4, 5003, 448, 1472),      # 15 rows, odd vocabulary, K in neither 8 nor 4 equal parts of 64
+    (11, 6, 5003, 512, 1472),     # 77 rows: 32 x 32 tiles on the LM head and gate/up, ragged in both directions
+])
+def test_small_f32_forward_ragged(B, k, vocab, hidden, ffn):
+    need_gpu()
+    shape = dataclasses.replace(synth.TINY, hidden=hidden, n_heads=6, n_kv_heads=2, ffn=ffn, vocab=vocab)
+    W = synth.model_weights(shape)
+    lens = 3 + 7 * np.arange(B)
+    caches = synth_caches(shape, lens, shape.n_layers)
+    tokens = synth.token_ids(B * (k + 1), vocab, 1, "ragged-f32").reshape(B, k + 1)
+    logits, hid = _gpu_forward(gm.DeviceModel(shape, W), device_cache(shape, caches, lens, k + 1), tokens)
+    ref, ref_h, _ = oracle.verify_forward(shape, W, caches, tokens, lens, EXACT)
+    # float32 sums over at most 1472 products through two layers: 1472 * 2^-24 = 9e-5 at worst
+    assert rel_err(logits, ref) < 9e-5
+    assert rel_err(hid, ref_h) < 9e-5
+
+
 @pytest.fixture(scope="module")
 def qwen_layer():
     wl = synth.WORKLOADS["qwen3_4b_layer"]
