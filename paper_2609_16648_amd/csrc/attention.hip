@@ -24,7 +24,7 @@
 //  * tiles wholly inside every query's causal window skip the mask; the
 //    online softmax (exp2 domain) rescales only when a running max grows by
 //    more than 2^kLazyLog2, so most tiles need no rescale.
-// float32 path: a plain wave-per-(row, head) kernel.
+// float32 path: a workgroup per (row, head), its four waves splitting the tokens.
 #include <atomic>
 
 #include "common.h"
@@ -459,58 +459,115 @@ struct AttnF {
   float scale;
 };
 
+// One workgroup of four waves per (block row, head, sequence).  A wave takes every fourth
+// chunk of 64 tokens with an online softmax of its own.  Scores: lane = token (8 channels
+// are contiguous in the K tile).  P V: lane = channel, D / 64 of them, and the chunk's
+// weights come back from LDS, so a lane's 16-byte load holds four tokens of its channel
+// and a wave's loads cover whole V tiles.  The wave partials are merged in wave order.
+// Bound by the chain of dependent loads, not by bytes (16 rows x 4 heads of 128 tokens:
+// 18 us with one wave per row whose lanes each walked the channels of their own tokens,
+// 6.8 us here).
 template <int D>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnF a) {
-  __shared__ float sm_m[64], sm_l[64];
-  __shared__ float sm_acc[64][D + 1];
-  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z, t = threadIdx.x;
+__global__ __launch_bounds__(256) void attn_f32_kernel(AttnF a) {
+  constexpr int C = D / 64;        // channels per lane in P V
+  __shared__ float sh_q[D];
+  __shared__ __attribute__((aligned(16))) float sh_p[4][64];
+  __shared__ float sh_m[4], sh_l[4], sh_o[4][D];
+  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blen = block_rows(a.blen, a.blen_add, b, a.R);
   float *orow = a.out + (((long)b * a.R + i) * a.n_heads + h) * D;
   if (i >= blen) {
-    for (int c = t; c < D; c += 64) orow[c] = 0.f;
+    for (int c = tid; c < D; c += 256) orow[c] = 0.f;
     return;
   }
   const int vis = a.base[b] + a.base_off + i + 1;
   const int kvh = h / a.G;
-  const float *qrow = a.q + (((long)b * a.R + i) * a.n_heads + h) * D;
-  float q[D], acc[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) { q[c] = qrow[c]; acc[c] = 0.f; }
-  float mx = -INFINITY, l = 0.f;
-  for (int tok = t; tok < vis; tok += 64) {
-    const int pi = tok / a.page_size;
+  for (int c = tid; c < D; c += 256) sh_q[c] = a.q[(((long)b * a.R + i) * a.n_heads + h) * D + c];
+  __syncthreads();
+  // the pool offset of tile tb (16 tokens, all in one page), or -1 for a page outside the pool
+  auto tile_base = [&](int tb) -> long {
+    const int pi = tb / a.page_size;
     const int page = pi < a.max_pages ? a.bt[(long)b * a.max_pages + pi] : -1;
-    if (page < 0 || page >= a.num_pages) {
-      raise_dev_err(a.dev_err, GM_DEVERR_PAGE);
-      break;
+    if (page < 0 || page >= a.num_pages) return -1;
+    return (((long)page * a.n_kv + kvh) * a.page_size + tb % a.page_size) * D;
+  };
+  float m = -INFINITY, l = 0.f, o[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) o[c] = 0.f;
+  for (int c0 = 64 * w; c0 < vis; c0 += 256) {
+    const int tok = c0 + lane;
+    float sc = -INFINITY;
+    if (tok < vis) {
+      const long tile = tile_base(tok & ~15);
+      if (tile < 0) {
+        raise_dev_err(a.dev_err, GM_DEVERR_PAGE);
+      } else {
+        const float *kt = a.kp + tile + (tok & 15) * 8;
+        sc = 0.f;
+#pragma unroll
+        for (int c = 0; c < D; c += 8) {
+          const floatx4u_t k0 = *reinterpret_cast<const floatx4u_t *>(kt + k_tile_off(0, c));
+          const floatx4u_t k1 = *reinterpret_cast<const floatx4u_t *>(kt + k_tile_off(0, c) + 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sc += sh_q[c + e] * k0[e];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sc += sh_q[c + 4 + e] * k1[e];
+        }
+        sc *= a.scale;
+      }
     }
-    const int off = tok % a.page_size;
-    const long tile = (((long)page * a.n_kv + kvh) * a.page_size + (off & ~15)) * D;
-    const int s = off & 15;
-    float sc = 0.f;
+    const float mn = fmaxf(m, wave_max(sc));
+    if (mn == -INFINITY) continue;   // no readable token in the chunk
+    const float p = expf(sc - mn), al = expf(m - mn);
+    l = l * al + wave_sum(p);
+    m = mn;
+    wave_lds_sync();                 // the last chunk's weights are read
+    sh_p[w][lane] = p;
+    wave_lds_sync();
 #pragma unroll
-    for (int c = 0; c < D; ++c) sc += q[c] * a.kp[tile + k_tile_off(s, c)];
-    sc *= a.scale;
-    const float mn = fmaxf(mx, sc);
-    const float al = expf(mx - mn), p = expf(sc - mn);
-    l = l * al + p;
+    for (int c = 0; c < C; ++c) o[c] *= al;
 #pragma unroll
-    for (int c = 0; c < D; ++c) acc[c] = acc[c] * al + p * a.vp[tile + v_tile_off(s, c)];
-    mx = mn;
+    for (int t = 0; t < 4; ++t) {
+      const int tb = c0 + 16 * t;
+      if (tb >= vis) break;
+      const long tile = tile_base(tb);
+      if (tile < 0) continue;
+#pragma unroll
+      for (int s = 0; s < 16; s += 4) {
+        const float4 pv = *reinterpret_cast<const float4 *>(&sh_p[w][16 * t + s]);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const floatx4u_t v = *reinterpret_cast<const floatx4u_t *>(a.vp + tile + v_tile_off(s, lane + 64 * c));
+          // slots past the visible tokens may hold anything
+          o[c] += pv.x * (tb + s < vis ? v[0] : 0.f);
+          o[c] += pv.y * (tb + s + 1 < vis ? v[1] : 0.f);
+          o[c] += pv.z * (tb + s + 2 < vis ? v[2] : 0.f);
+          o[c] += pv.w * (tb + s + 3 < vis ? v[3] : 0.f);
+        }
+      }
+    }
   }
-  sm_m[t] = mx;
-  sm_l[t] = l;
+  if (lane == 0) {
+    sh_m[w] = m;
+    sh_l[w] = l;
+  }
 #pragma unroll
-  for (int c = 0; c < D; ++c) sm_acc[t][c] = acc[c];
+  for (int c = 0; c < C; ++c) sh_o[w][lane + 64 * c] = o[c];
   __syncthreads();
   float M = -INFINITY;
-  for (int u = 0; u < 64; ++u) M = fmaxf(M, sm_m[u]);
-  float den = 0.f;
-  for (int u = 0; u < 64; ++u) den += sm_m[u] == -INFINITY ? 0.f : sm_l[u] * expf(sm_m[u] - M);
-  for (int c = t; c < D; c += 64) {
-    float num = 0.f;
-    for (int u = 0; u < 64; ++u) num += sm_m[u] == -INFINITY ? 0.f : sm_acc[u][c] * expf(sm_m[u] - M);
-    orow[c] = num / den;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) M = fmaxf(M, sh_m[u]);
+  if (tid < D) {
+    float den = 0.f, num = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (sh_m[u] == -INFINITY) continue;
+      const float f = expf(sh_m[u] - M);
+      den += sh_l[u] * f;
+      num += sh_o[u][tid] * f;
+    }
+    orow[tid] = num / den;
   }
 }
 
@@ -676,8 +733,8 @@ void run_attention(const AttnArgs &a, const AttnPlan &p, char *ws, hipStream_t s
     f.scale = a.scale;
     dim3 grid(a.R, a.n_heads, a.B);
     TraceScope ts(a.trace, s);
-    if (a.head_dim == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64), 0, s, f);
-    else hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64), 0, s, f);
+    if (a.head_dim == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, s, f);
+    else hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, s, f);
   }
 }
 

@@ -73,6 +73,19 @@ def test_f32_attention_matches_oracle():
     assert e < 1e-4
 
 
+@pytest.mark.parametrize("head_dim,n_kv,page_size,lens,k", [
+    (64, 4, 16, [0, 1, 15, 60, 61, 62, 253, 254, 255], 2),     # edges of 16-token tiles, 64-token chunks, the 4 waves
+    (128, 2, 32, [0, 63, 192, 256, 700, 1029], 1),             # two channels per lane, GQA, several rounds
+])
+def test_f32_attention_chunk_edges(head_dim, n_kv, page_size, lens, k):
+    need_gpu()
+    shape = dataclasses.replace(synth.TINY, head_dim=head_dim, n_kv_heads=n_kv)
+    got, ref, _ = _case(shape, np.array(lens), k, page_size, seed=31 + head_dim)
+    # a score is a float32 sum of head_dim products of N(0, 1) values over sqrt(head_dim): its error
+    # is below head_dim * 2^-24 * (a few) = 2e-5, which moves each weight by as much, relatively
+    assert rel_err(got, ref) < 2e-5
+
+
 def test_gqa_group_of_eight_and_odd_rows():
     # 32 query heads on 4 KV heads with k = 2: 24 rows in two 16-row tiles
     need_gpu()
