@@ -211,7 +211,7 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
   const int rows = a.G * a.R;
 
   __shared__ int scan_sh[16];
-  __shared__ int page_sh[kAttnMaxSplitPages];
+  __shared__ int page_sh[kAttnWinPages];
   __shared__ int bad_sh, first_sh, first_cum_sh;
 
   // Total tiles TT, then the first sequence of this workgroup's range [s, e): a chunked
@@ -273,33 +273,6 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
     if (ta >= tz) continue;
     const int t0 = 16 * ta, t1 = min(L, 16 * tz);
 
-    // The pages of [t0, t1), looked up once into LDS: in the loop a lookup is then an LDS
-    // read, whose counter is separate from the KV loads', so no wait drains the prefetch.
-    // A page outside the pool ends the segment before its first token (and is reported).
-    const int p0 = t0 / a.page_size;
-    int np = (t1 - 1) / a.page_size - p0 + 1;
-    __syncthreads();   // the previous segment is done with page_sh
-    if (threadIdx.x == 0) bad_sh = np;
-    if (np > kAttnMaxSplitPages) {   // lengths beyond the planned maximum: stop at the table's end
-      np = kAttnMaxSplitPages;
-      if (threadIdx.x == 0) bad_sh = np;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < np; i += blockDim.x) {
-      const int pi = p0 + i;
-      const int page = pi < a.max_pages ? a.bt[(long)b * a.max_pages + pi] : -1;
-      page_sh[i] = page;
-      if (page < 0 || page >= a.num_pages) atomicMin(&bad_sh, i);
-    }
-    __syncthreads();
-    if (!wave_ok) continue;   // spare waves of the last head group (they still join the barriers)
-    int tend = t1;
-    const int bad = __builtin_amdgcn_readfirstlane(bad_sh);
-    if (bad < (t1 - 1) / a.page_size - p0 + 1) {
-      raise_dev_err(a.dev_err, GM_DEVERR_PAGE);
-      tend = max(t0, (p0 + bad) * a.page_size);
-    }
-
     bf16x8_t qf[RT][4];
     int vis[RT];
     float m[RT], l[RT];
@@ -308,7 +281,7 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
     for (int u = 0; u < RT; ++u) {
       const int r = (rt0 + u) * 16 + j;
       vis[u] = 0;
-      if (r < rows) {
+      if (r < rows && wave_ok) {
         const int hl = r / a.R, i = r % a.R;
         const uint16_t *qrow = a.q + (((long)b * a.R + i) * a.n_heads + kvh * a.G + hl) * 128;
 #pragma unroll
@@ -324,54 +297,83 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
       for (int mm = 0; mm < 8; ++mm) O[u][mm] = floatx4_t{0.f, 0.f, 0.f, 0.f};
     }
 
-    auto tile_off = [&](int tb) -> long {
-      const int page = page_sh[tb / a.page_size - p0];
-      return (long)page * a.n_kv * a.page_size * 128 + head_off + (long)(tb % a.page_size) * 128;
-    };
-    auto load_tile = [&](long off, TileBuf &t) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) t.k[i] = load_kv<STREAM>(a.kp + off + i * 512 + lane * 8);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) t.v[i] = load_kv<STREAM>(a.vp + off + i * 512 + lane * 8);
-    };
-
-    // Tiles [t0, t0 + 16 n) lie below position m0 + 1, inside the window of every valid
-    // query row, and inside the context: no mask.  The rest (the causal diagonal and the
-    // partial tile at the end of the context) take the mask; the mask zeroes the V entries
-    // past the context in place.  Rows that are not valid queries (past the block, or
-    // padding) compute finite values nobody reads.  All nt tiles stream through the ring,
-    // the masked ones too, so the segment's end is as pipelined as its body.
-    const int nm_end = min(tend, m0 + 1);
-    const int n = __builtin_amdgcn_readfirstlane(nm_end > t0 ? (nm_end - t0) / 16 : 0);
-    const int nt = __builtin_amdgcn_readfirstlane(tend > t0 ? (tend - t0 + 15) / 16 : 0);
-    auto consume = [&](int i, TileBuf &t) {
-      if (i < n) attn_tiles<false, RT>(t0 + 16 * i, L, g, a.scale_log2, t, qf, vis, m, l, O);
-      else attn_tiles<true, RT>(t0 + 16 * i, L, g, a.scale_log2, t, qf, vis, m, l, O);
-    };
-    if (nt > 0) {
-      // whole turns of the ring run unguarded (one straight path, so every wait counts
-      // exactly the loads still in flight); the last < kAttnRing tiles are already in
-      // the ring when the loop ends
-      TileBuf ring[kAttnRing];
-      const int n_pipe = nt - nt % kAttnRing;
-#pragma unroll
-      for (int d = 0; d < kAttnRing - 1; ++d) load_tile(tile_off(t0 + 16 * min(d, nt - 1)), ring[d]);
-      for (int i = 0; i < n_pipe; i += kAttnRing) {
-#pragma unroll
-        for (int d = 0; d < kAttnRing; ++d) {
-          // refill the buffer consumed last step (a re-read of the last tile near the end);
-          // the scheduling barriers keep each refill after the step that frees its buffer,
-          // so the ring keeps fixed registers and no copy waits on a load in flight
-          __builtin_amdgcn_sched_barrier(0);
-          load_tile(tile_off(t0 + 16 * min(i + d + kAttnRing - 1, nt - 1)), ring[(d + kAttnRing - 1) % kAttnRing]);
-          __builtin_amdgcn_sched_barrier(0);
-          consume(i + d, ring[d]);
-        }
+    // The segment [t0, t1) in windows of whole pages, at most kAttnWinPages of them, whose page
+    // ids are looked up once into LDS: in the loop a lookup is then an LDS read, whose counter
+    // is separate from the KV loads', so no wait drains the prefetch.  A page outside the pool
+    // ends the segment before its first token (and is reported).
+    for (int w0 = t0; w0 < t1;) {
+      const int p0 = w0 / a.page_size;
+      const int w1 = (int)min((long)t1, (long)(p0 + kAttnWinPages) * a.page_size);
+      const int np = (w1 - 1) / a.page_size - p0 + 1;
+      __syncthreads();   // the previous window is done with page_sh
+      if (threadIdx.x == 0) bad_sh = np;
+      __syncthreads();
+      for (int i = threadIdx.x; i < np; i += blockDim.x) {
+        const int pi = p0 + i;
+        const int page = pi < a.max_pages ? a.bt[(long)b * a.max_pages + pi] : -1;
+        page_sh[i] = page;
+        if (page < 0 || page >= a.num_pages) atomicMin(&bad_sh, i);
       }
+      __syncthreads();
+      const int bad = __builtin_amdgcn_readfirstlane(bad_sh);
+      int tend = w1;
+      if (bad < np) tend = max(w0, (p0 + bad) * a.page_size);
+
+      auto tile_off = [&](int tb) -> long {
+        const int page = page_sh[tb / a.page_size - p0];
+        return (long)page * a.n_kv * a.page_size * 128 + head_off + (long)(tb % a.page_size) * 128;
+      };
+      auto load_tile = [&](long off, TileBuf &t) {
 #pragma unroll
-      for (int d = 0; d < kAttnRing - 1; ++d)
-        if (n_pipe + d < nt) consume(n_pipe + d, ring[d]);
+        for (int i = 0; i < 4; ++i) t.k[i] = load_kv<STREAM>(a.kp + off + i * 512 + lane * 8);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t.v[i] = load_kv<STREAM>(a.vp + off + i * 512 + lane * 8);
+      };
+
+      // Tiles [w0, w0 + 16 n) lie below position m0 + 1, inside the window of every valid
+      // query row, and inside the context: no mask.  The rest (the causal diagonal and the
+      // partial tile at the end of the context) take the mask; the mask zeroes the V entries
+      // past the context in place.  Rows that are not valid queries (past the block, or
+      // padding) compute finite values nobody reads.  All nt tiles stream through the ring,
+      // the masked ones too, so the segment's end is as pipelined as its body.
+      const int nm_end = min(tend, m0 + 1);
+      const int n = __builtin_amdgcn_readfirstlane(nm_end > w0 ? (nm_end - w0) / 16 : 0);
+      const int nt = __builtin_amdgcn_readfirstlane(wave_ok && tend > w0 ? (tend - w0 + 15) / 16 : 0);
+      auto consume = [&](int i, TileBuf &t) {
+        if (i < n) attn_tiles<false, RT>(w0 + 16 * i, L, g, a.scale_log2, t, qf, vis, m, l, O);
+        else attn_tiles<true, RT>(w0 + 16 * i, L, g, a.scale_log2, t, qf, vis, m, l, O);
+      };
+      if (nt > 0) {
+        // whole turns of the ring run unguarded (one straight path, so every wait counts
+        // exactly the loads still in flight); the last < kAttnRing tiles are already in
+        // the ring when the loop ends
+        TileBuf ring[kAttnRing];
+        const int n_pipe = nt - nt % kAttnRing;
+#pragma unroll
+        for (int d = 0; d < kAttnRing - 1; ++d) load_tile(tile_off(w0 + 16 * min(d, nt - 1)), ring[d]);
+        for (int i = 0; i < n_pipe; i += kAttnRing) {
+#pragma unroll
+          for (int d = 0; d < kAttnRing; ++d) {
+            // refill the buffer consumed last step (a re-read of the last tile near the end);
+            // the scheduling barriers keep each refill after the step that frees its buffer,
+            // so the ring keeps fixed registers and no copy waits on a load in flight
+            __builtin_amdgcn_sched_barrier(0);
+            load_tile(tile_off(w0 + 16 * min(i + d + kAttnRing - 1, nt - 1)), ring[(d + kAttnRing - 1) % kAttnRing]);
+            __builtin_amdgcn_sched_barrier(0);
+            consume(i + d, ring[d]);
+          }
+        }
+#pragma unroll
+        for (int d = 0; d < kAttnRing - 1; ++d)
+          if (n_pipe + d < nt) consume(n_pipe + d, ring[d]);
+      }
+      if (bad < np) {
+        if (wave_ok) raise_dev_err(a.dev_err, GM_DEVERR_PAGE);
+        break;
+      }
+      w0 = w1;
     }
+    if (!wave_ok) continue;   // spare waves of the last head group (they only join the barriers)
 
 #pragma unroll
     for (int u = 0; u < RT; ++u) {
@@ -624,10 +626,10 @@ AttnPlan plan_attention(const gm_model_config &cfg, int B, int R, int max_ctx) {
   if (cfg.dtype != GM_BF16) return p;
   const AttnGeom g = attn_geom(cfg, p.rows_pad);
   long parts = resident_groups(g.block) / g.groups;
-  // bound the tiles of one range so its pages fit the workgroup's page table
-  const long tiles_max = (long)B * (((long)max_ctx + R + 15) / 16);
-  const long need = (tiles_max + kAttnMaxSplitTokens / 16 - 1) / (kAttnMaxSplitTokens / 16);
-  if (parts < need) parts = need;
+  // One range per workgroup that the chip holds, however long: every further round of workgroups
+  // fills its rings again, writes more partials, and the last one leaves CUs idle (256 sequences
+  // of 512-8704 tokens: 840 us with one round, 898 us in 4.25 rounds of at most 4096 tokens;
+  // 32 sequences of 16-32K tokens: 500 us with one round, 530 with two, 577 with four).
   if (parts < 1) parts = 1;
   p.parts = (int)parts;
   Carve c;

@@ -8,8 +8,7 @@ namespace gm {
 
 constexpr int kMaxRowFloats = 16384;   // float32 row that the row kernels stage in LDS (64 KiB)
 constexpr int kAttnMaxRows = 64;   // (n_heads / n_kv_heads) * block rows per KV head
-constexpr int kAttnMaxSplitTokens = 4096;                           // tokens of one workgroup's range
-constexpr int kAttnMaxSplitPages = kAttnMaxSplitTokens / 16 + 8;    // pages one range can touch
+constexpr int kAttnWinPages = 256; // page ids that a workgroup of the attention holds in LDS at a time
 
 struct Carve {
   size_t off = 0;

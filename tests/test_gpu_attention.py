@@ -64,6 +64,18 @@ def test_bf16_attention_long_context():
     assert e < 2e-2
 
 
+@pytest.mark.parametrize("lens,k,page_size", [
+    ([20000] + [0, 17, 1] * 100, 0, 32),    # more sequences than threads of a workgroup, many in one range
+    ([3] * 256, 3, 16),                     # one tile each: fewer tiles than workgroups times heads
+    ([500, 0, 0, 9000, 31], 1, 16),
+])
+def test_bf16_attention_many_sequences(lens, k, page_size):
+    need_gpu()
+    shape = dataclasses.replace(synth.QWEN3_4B_LAYER, n_heads=12, n_kv_heads=6)   # a head group with spare waves
+    got, ref, _ = _case(shape, np.array(lens), k, page_size, seed=41 + k)
+    assert np.abs(got - oracle.round_bf16(ref)).max() <= 2.0 ** -7 * np.abs(ref).max()
+
+
 def test_f32_attention_matches_oracle():
     need_gpu()
     shape = synth.TINY
