@@ -5,8 +5,10 @@
 // to end, are cut into P equal ranges, P = the number of workgroups the chip
 // holds at once; workgroup (p, head group) takes range p for its heads, so
 // every wave streams the same number of tiles whatever the length mix, and a
-// range that crosses sequences yields one partial per sequence.  A combine
-// kernel merges the partials of each sequence.  One 64-lane wave per KV head and
+// range that crosses sequences streams on from one to the next without draining.
+// A sequence inside one range is written as it is; a range that holds part of one
+// yields a partial, and a combine kernel merges the partials of each such
+// sequence.  One 64-lane wave per KV head and
 // one or two 16-row query tiles (two: the k = 7 block, 32 rows, streams each KV
 // tile once for both):
 //  * GQA packing: the (n_heads / n_kv_heads) query heads of one KV head times
@@ -34,11 +36,13 @@ namespace gm {
 
 namespace {
 constexpr int kAttnWavesPerGroup = 4;   // waves per workgroup (KV heads x query row tiles)
-// Dynamic LDS a workgroup reserves (unused) so that a CU holds one at a time:
-// with two per CU the older one wins the SIMD arbitration, finishes early and
-// leaves the CU half idle for the rest of the launch (measured); one per CU
-// keeps all ranges in step.
+// Dynamic LDS a workgroup reserves so that a CU holds one at a time: with two
+// per CU the older one wins the SIMD arbitration, finishes early and leaves the
+// CU half idle for the rest of the launch (measured); one per CU keeps all ranges
+// in step.  Each wave uses a slice of 16 rows of kAttnRowPad floats of it.
 constexpr int kAttnLdsReserve = 84 * 1024;
+constexpr int kAttnRowPad = 132;        // floats between rows of an output tile in LDS (128 + 4: distinct banks)
+static_assert(kAttnWavesPerGroup * 16 * kAttnRowPad * 4 <= kAttnLdsReserve, "the waves' slices fit the reservation");
 constexpr int kAttnRing = 3;            // K/V register buffers per wave
 constexpr float kLazyLog2 = 8.f;        // rescale threshold of the running max (log2 units)
 
@@ -46,6 +50,7 @@ struct AttnK {
   const uint16_t *kp, *vp;
   const int32_t *bt, *base, *blen;
   const uint16_t *q;
+  uint16_t *out;
   float *part_o;        // [P + B slots][n_kv][rows_pad][128]
   float2 *part_ml;      // [P + B slots][n_kv][rows_pad]
   int32_t *cum;         // [B + 1] tiles before sequence b (written by workgroup (0, 0))
@@ -108,6 +113,7 @@ __device__ __forceinline__ uint4 load_kv(const uint16_t *p) {
 
 struct TileBuf {
   uint4 k[4], v[4];
+  int slot;   // the tile's place in the pool, -1: none
 };
 
 // One 16-token tile for the RT 16-row query tiles of a wave: S^T = K Q^T, online softmax,
@@ -210,185 +216,242 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
   const bool wave_ok = kvh < a.n_kv;
   const int rows = a.G * a.R;
 
+  // Sequences come in chunks of blockDim.x, one per thread; the tiles of a chunk that fall in
+  // the range stream in windows of kAttnWinTiles.
   __shared__ int scan_sh[16];
-  __shared__ int page_sh[kAttnWinPages];
-  __shared__ int bad_sh, first_sh, first_cum_sh;
+  __shared__ int cum_sh[64 * kAttnWavesPerGroup + 1];                        // tiles before each sequence of the chunk
+  __shared__ int m0_sh[64 * kAttnWavesPerGroup], bl_sh[64 * kAttnWavesPerGroup];   // block start and valid block rows
+  __shared__ int slot_sh[kAttnWinTiles], seq_sh[kAttnWinTiles];              // per tile: place in the pool, sequence
 
-  // Total tiles TT, then the first sequence of this workgroup's range [s, e): a chunked
-  // block scan over the sequences (workgroup (0, 0) also stores the prefix sums for the
-  // combine).  Every workgroup computes the same sums.
-  // (a batch that fits one block needs a single scan)
-  const bool one_chunk = a.B <= (int)blockDim.x;
+  // Total tiles TT over all sequences; every workgroup computes the same sums, and workgroup
+  // (0, 0) also stores the prefix sums for the combine.
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  const bool one_chunk = a.B <= nthr;   // a batch that fits one block needs a single scan
+  const bool writer = part == 0 && grp == 0;
   int TT = 0, T1 = 0, cb1 = 0;
   if (one_chunk) {
-    T1 = (int)threadIdx.x < a.B ? seq_tiles(a, threadIdx.x) : 0;
+    T1 = tid < a.B ? seq_tiles(a, tid) : 0;
     cb1 = block_excl_scan(T1, scan_sh, &TT);
+    if (writer && tid < a.B) a.cum[tid] = cb1;
   } else {
-    for (int c = 0; c < a.B; c += blockDim.x) {
-      const int b = c + threadIdx.x;
+    for (int c = 0; c < a.B; c += nthr) {
+      const int T = c + tid < a.B ? seq_tiles(a, c + tid) : 0;
       int tot;
-      block_excl_scan(b < a.B ? seq_tiles(a, b) : 0, scan_sh, &tot);
+      const int cb = TT + block_excl_scan(T, scan_sh, &tot);
+      if (writer && c + tid < a.B) a.cum[c + tid] = cb;
       TT += tot;
     }
   }
+  if (writer && tid == 0) a.cum[a.B] = TT;
   const int s = part_begin(part, TT, a.parts), e = part_begin(part + 1, TT, a.parts);
-  if (threadIdx.x == 0) first_sh = a.B;
-  __syncthreads();
-  const bool writer = part == 0 && grp == 0;
-  auto visit = [&](int b, int T, int cb) {
-    if (b >= a.B) return;
-    if (writer) a.cum[b] = cb;
-    if (T > 0 && cb <= s && s < cb + T) {   // the sequence holding tile s (unique)
-      first_sh = b;
-      first_cum_sh = cb;
-    }
-  };
-  if (one_chunk) {
-    visit(threadIdx.x, T1, cb1);
-  } else {
-    int run = 0;
-    for (int c = 0; c < a.B; c += blockDim.x) {
-      const int b = c + threadIdx.x;
-      const int T = b < a.B ? seq_tiles(a, b) : 0;
-      int tot;
-      const int cb = run + block_excl_scan(T, scan_sh, &tot);
-      visit(b, T, cb);
-      run += tot;
-    }
-  }
-  if (writer && threadIdx.x == 0) a.cum[a.B] = TT;
-  __syncthreads();
   if (s >= e) return;   // an empty range (fewer tiles than workgroups)
-  int b = __builtin_amdgcn_readfirstlane(first_sh);
-  int cb = __builtin_amdgcn_readfirstlane(first_cum_sh);
+  const int tpp = a.page_size >> 4;                        // tiles per page
   const long head_off = (long)kvh * a.page_size * 128;
 
-  for (; b < a.B && cb < e; ++b) {
-    const int m0 = __builtin_amdgcn_readfirstlane(a.base[b] + a.base_off);
-    const int blen = __builtin_amdgcn_readfirstlane(block_rows(a.blen, a.blen_add, b, a.R));
-    const int L = m0 + blen;
-    const int T = L > 0 ? (L + 15) >> 4 : 0;
-    const int ta = max(s, cb) - cb, tz = min(e, cb + T) - cb;
-    cb += T;
-    if (ta >= tz) continue;
-    const int t0 = 16 * ta, t1 = min(L, 16 * tz);
+  // this lane's query rows: row (rt0 + u) * 16 + j of the head's G x R rows
+  int qrow[RT], qi[RT];
+#pragma unroll
+  for (int u = 0; u < RT; ++u) {
+    const int r = (rt0 + u) * 16 + j;
+    qi[u] = r < rows && wave_ok ? r % a.R : -1;
+    qrow[u] = qi[u] >= 0 ? (qi[u] * a.n_heads + kvh * a.G + r / a.R) * 128 + 8 * g : 0;
+  }
+  auto load_q = [&](int b, bf16x8_t (&q)[RT][4]) {
+    const uint16_t *qb = a.q + (long)b * a.R * a.n_heads * 128;
+#pragma unroll
+    for (int u = 0; u < RT; ++u)
+#pragma unroll
+      for (int ii = 0; ii < 4; ++ii)
+        q[u][ii] = as_bf16x8(qi[u] >= 0 ? *reinterpret_cast<const uint4 *>(qb + qrow[u] + 32 * ii) : make_uint4(0, 0, 0, 0));
+  };
 
-    bf16x8_t qf[RT][4];
-    int vis[RT];
-    float m[RT], l[RT];
-    floatx4_t O[RT][8];
-#pragma unroll
-    for (int u = 0; u < RT; ++u) {
-      const int r = (rt0 + u) * 16 + j;
-      vis[u] = 0;
-      if (r < rows && wave_ok) {
-        const int hl = r / a.R, i = r % a.R;
-        const uint16_t *qrow = a.q + (((long)b * a.R + i) * a.n_heads + kvh * a.G + hl) * 128;
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) qf[u][ii] = as_bf16x8(*reinterpret_cast<const uint4 *>(qrow + 32 * ii + 8 * g));
-        vis[u] = i < blen ? m0 + i + 1 : 0;
-      } else {
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) qf[u][ii] = as_bf16x8(make_uint4(0, 0, 0, 0));
-      }
-      m[u] = -INFINITY;
-      l[u] = 0.f;
-#pragma unroll
-      for (int mm = 0; mm < 8; ++mm) O[u][mm] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    }
-
-    // The segment [t0, t1) in windows of whole pages, at most kAttnWinPages of them, whose page
-    // ids are looked up once into LDS: in the loop a lookup is then an LDS read, whose counter
-    // is separate from the KV loads', so no wait drains the prefetch.  A page outside the pool
-    // ends the segment before its first token (and is reported).
-    for (int w0 = t0; w0 < t1;) {
-      const int p0 = w0 / a.page_size;
-      const int w1 = (int)min((long)t1, (long)(p0 + kAttnWinPages) * a.page_size);
-      const int np = (w1 - 1) / a.page_size - p0 + 1;
-      __syncthreads();   // the previous window is done with page_sh
-      if (threadIdx.x == 0) bad_sh = np;
-      __syncthreads();
-      for (int i = threadIdx.x; i < np; i += blockDim.x) {
-        const int pi = p0 + i;
-        const int page = pi < a.max_pages ? a.bt[(long)b * a.max_pages + pi] : -1;
-        page_sh[i] = page;
-        if (page < 0 || page >= a.num_pages) atomicMin(&bad_sh, i);
-      }
-      __syncthreads();
-      const int bad = __builtin_amdgcn_readfirstlane(bad_sh);
-      int tend = w1;
-      if (bad < np) tend = max(w0, (p0 + bad) * a.page_size);
-
-      auto tile_off = [&](int tb) -> long {
-        const int page = page_sh[tb / a.page_size - p0];
-        return (long)page * a.n_kv * a.page_size * 128 + head_off + (long)(tb % a.page_size) * 128;
-      };
-      auto load_tile = [&](long off, TileBuf &t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) t.k[i] = load_kv<STREAM>(a.kp + off + i * 512 + lane * 8);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) t.v[i] = load_kv<STREAM>(a.vp + off + i * 512 + lane * 8);
-      };
-
-      // Tiles [w0, w0 + 16 n) lie below position m0 + 1, inside the window of every valid
-      // query row, and inside the context: no mask.  The rest (the causal diagonal and the
-      // partial tile at the end of the context) take the mask; the mask zeroes the V entries
-      // past the context in place.  Rows that are not valid queries (past the block, or
-      // padding) compute finite values nobody reads.  All nt tiles stream through the ring,
-      // the masked ones too, so the segment's end is as pipelined as its body.
-      const int nm_end = min(tend, m0 + 1);
-      const int n = __builtin_amdgcn_readfirstlane(nm_end > w0 ? (nm_end - w0) / 16 : 0);
-      const int nt = __builtin_amdgcn_readfirstlane(wave_ok && tend > w0 ? (tend - w0 + 15) / 16 : 0);
-      auto consume = [&](int i, TileBuf &t) {
-        if (i < n) attn_tiles<false, RT>(w0 + 16 * i, L, g, a.scale_log2, t, qf, vis, m, l, O);
-        else attn_tiles<true, RT>(w0 + 16 * i, L, g, a.scale_log2, t, qf, vis, m, l, O);
-      };
-      if (nt > 0) {
-        // whole turns of the ring run unguarded (one straight path, so every wait counts
-        // exactly the loads still in flight); the last < kAttnRing tiles are already in
-        // the ring when the loop ends
-        TileBuf ring[kAttnRing];
-        const int n_pipe = nt - nt % kAttnRing;
-#pragma unroll
-        for (int d = 0; d < kAttnRing - 1; ++d) load_tile(tile_off(w0 + 16 * min(d, nt - 1)), ring[d]);
-        for (int i = 0; i < n_pipe; i += kAttnRing) {
-#pragma unroll
-          for (int d = 0; d < kAttnRing; ++d) {
-            // refill the buffer consumed last step (a re-read of the last tile near the end);
-            // the scheduling barriers keep each refill after the step that frees its buffer,
-            // so the ring keeps fixed registers and no copy waits on a load in flight
-            __builtin_amdgcn_sched_barrier(0);
-            load_tile(tile_off(w0 + 16 * min(i + d + kAttnRing - 1, nt - 1)), ring[(d + kAttnRing - 1) % kAttnRing]);
-            __builtin_amdgcn_sched_barrier(0);
-            consume(i + d, ring[d]);
-          }
-        }
-#pragma unroll
-        for (int d = 0; d < kAttnRing - 1; ++d)
-          if (n_pipe + d < nt) consume(n_pipe + d, ring[d]);
-      }
-      if (bad < np) {
-        if (wave_ok) raise_dev_err(a.dev_err, GM_DEVERR_PAGE);
-        break;
-      }
-      w0 = w1;
-    }
-    if (!wave_ok) continue;   // spare waves of the last head group (they only join the barriers)
-
+  // The segment (the tiles of one sequence in this range) being streamed: sequence, block
+  // start, context, tiles before the sequence and up to its end, end of the segment; the queries, the softmax state, and the
+  // queries of the next segment, loaded one segment ahead.
+  int b = -1, m0 = 0, L = 0, cb = 0, seq_end = 0, seg_end = s;
+  bool dead = false, have_next = false;
+  bf16x8_t qf[RT][4], qn[RT][4];
+  int vis[RT];
+  float m[RT], l[RT];
+  floatx4_t O[RT][8];
+  // The end of a segment.  A sequence that lies wholly in this range is normalised and written
+  // as it is (the combine skips it); a part of one goes to the partials.  The rows pass through
+  // this wave's slice of LDS so that every store covers whole lines: stores of the 16 or 64
+  // bytes a lane group holds of a row, for padding rows too, held the KV stream up by 25 us per
+  // segment (1024 sequences of 2560 tokens: 1784 us with them, 1598 us here).
+  extern __shared__ __attribute__((aligned(16))) float attn_sh[];   // kAttnLdsReserve bytes
+  float *const rows_sh = attn_sh + w * 16 * kAttnRowPad;
+  auto finish = [&]() __attribute__((always_inline)) {
+    const bool whole = cb >= s && seq_end <= e;
 #pragma unroll
     for (int u = 0; u < RT; ++u) {
       float lu = l[u];
       lu += __shfl_xor(lu, 16, kWave);
       lu += __shfl_xor(lu, 32, kWave);
-      const long prow = ((long)(part + b) * a.n_kv + kvh) * a.rows_pad + (rt0 + u) * 16 + j;
-      if (g == 0) a.part_ml[prow] = make_float2(m[u], lu);
-      float *po = a.part_o + prow * 128;
+      const long prow0 = ((long)(part + b) * a.n_kv + kvh) * a.rows_pad + (rt0 + u) * 16;
+      if (!whole && g == 0) a.part_ml[prow0 + j] = make_float2(m[u], lu);
+      // rows with no visible token (past the block, or none readable) give 0
+      const bool live = vis[u] > 0 && m[u] != -INFINITY;
+      const float inv = 1.f / lu;
+      wave_lds_sync();
 #pragma unroll
-      for (int mm = 0; mm < 8; ++mm)
-        *reinterpret_cast<float4 *>(po + 16 * mm + 4 * g) =
-            make_float4(O[u][mm][0], O[u][mm][1], O[u][mm][2], O[u][mm][3]);
+      for (int mm = 0; mm < 8; ++mm) {
+        floatx4_t v = O[u][mm];
+        if (whole) v = live ? v * inv : floatx4_t{0.f, 0.f, 0.f, 0.f};
+        *reinterpret_cast<floatx4_t *>(rows_sh + j * kAttnRowPad + 16 * mm + 4 * g) = v;
+      }
+      wave_lds_sync();
+      const int nr = min(16, rows - (rt0 + u) * 16);   // rows of this tile that exist
+      if (whole) {
+#pragma unroll 1   // (the segment's end is inlined at every ring position: short code counts here)
+        for (int q = 0; q < 4; ++q) {
+          const int rl = 4 * q + g, r = (rt0 + u) * 16 + rl;
+          if (rl >= nr) continue;
+          const float *src = rows_sh + rl * kAttnRowPad + 8 * j;
+          uint32_t pk[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            pk[c] = f32_to_bf16(src[2 * c]) | (uint32_t(f32_to_bf16(src[2 * c + 1])) << 16);
+          const long o = (((long)b * a.R + r % a.R) * a.n_heads + kvh * a.G + r / a.R) * 128 + 8 * j;
+          *reinterpret_cast<uint4 *>(a.out + o) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        }
+      } else {
+#pragma unroll 2
+        for (int q = 0; q < 8; ++q) {
+          const int rl = 2 * q + (lane >> 5), c = 4 * (lane & 31);
+          if (rl < nr)
+            *reinterpret_cast<floatx4_t *>(a.part_o + (prow0 + rl) * 128 + c) =
+                *reinterpret_cast<const floatx4_t *>(rows_sh + rl * kAttnRowPad + c);
+        }
+      }
+    }
+  };
+
+  int run = 0;
+  for (int c = 0; c < a.B; c += nthr) {
+    int T, cbt, tot;
+    if (one_chunk) {
+      T = T1;
+      cbt = cb1;
+      tot = TT;
+    } else {
+      T = c + tid < a.B ? seq_tiles(a, c + tid) : 0;
+      cbt = run + block_excl_scan(T, scan_sh, &tot);
+    }
+    const int cbeg = run, cend = run + tot;
+    run = cend;
+    if (cend <= s) continue;
+    if (cbeg >= e) break;
+    __syncthreads();   // the previous chunk's tables are read
+    cum_sh[tid] = cbt;
+    if (tid == 0) cum_sh[nthr] = cend;
+    if (T > 0) {
+      m0_sh[tid] = a.base[c + tid] + a.base_off;
+      bl_sh[tid] = block_rows(a.blen, a.blen_add, c + tid, a.R);
+    }
+    const int xe = min(e, cend);
+    for (int x0 = max(s, cbeg); x0 < xe; x0 += kAttnWinTiles) {
+      const int nt = min(kAttnWinTiles, xe - x0);
+      // The window's tiles, looked up once into LDS: in the loop a lookup is then an LDS read,
+      // whose counter is separate from the KV loads', so no wait drains the prefetch.  A page
+      // outside the pool is reported; it ends its segment before its first token.
+      __syncthreads();
+      for (int i = tid; i < nt; i += nthr) {
+        int lo = 0, hi = nthr;   // the last sequence with at most x0 + i tiles before it
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (cum_sh[mid] <= x0 + i) lo = mid;
+          else hi = mid;
+        }
+        const int t = x0 + i - cum_sh[lo], pi = t / tpp;
+        const int page = pi < a.max_pages ? a.bt[(long)(c + lo) * a.max_pages + pi] : -1;
+        const bool ok = page >= 0 && page < a.num_pages;
+        if (!ok) raise_dev_err(a.dev_err, GM_DEVERR_PAGE);
+        seq_sh[i] = lo;
+        slot_sh[i] = ok ? page * a.n_kv * tpp + t % tpp : -1;   // 16 x 128 elements each, of the first head
+      }
+      __syncthreads();
+      if (!wave_ok) continue;   // spare waves of the last head group (they only join the barriers)
+
+      // A bad tile loads the pool's first tile instead; its segment is not consumed further.
+      auto load_tile = [&](int i, TileBuf &t) {
+        t.slot = __builtin_amdgcn_readfirstlane(slot_sh[i]);
+        const long off = head_off + (long)max(t.slot, 0) * 2048;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t.k[q] = load_kv<STREAM>(a.kp + off + q * 512 + lane * 8);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t.v[q] = load_kv<STREAM>(a.vp + off + q * 512 + lane * 8);
+      };
+      auto step = [&](int i, TileBuf &t) __attribute__((always_inline)) {
+        if (i >= nt) return;
+        const int x = x0 + i;
+        if (x == seg_end) {   // the first tile of a segment
+          if (b >= 0) finish();
+          const int q = __builtin_amdgcn_readfirstlane(seq_sh[i]);
+          b = c + q;
+          m0 = __builtin_amdgcn_readfirstlane(m0_sh[q]);
+          const int blen = __builtin_amdgcn_readfirstlane(bl_sh[q]);
+          L = m0 + blen;
+          cb = __builtin_amdgcn_readfirstlane(cum_sh[q]);
+          seq_end = __builtin_amdgcn_readfirstlane(cum_sh[q + 1]);
+          seg_end = min(e, seq_end);
+          dead = false;
+          if (have_next) {
+#pragma unroll
+            for (int u = 0; u < RT; ++u)
+#pragma unroll
+              for (int ii = 0; ii < 4; ++ii) qf[u][ii] = qn[u][ii];
+          } else {
+            load_q(b, qf);
+          }
+          // the queries have arrived before the paths join, or every tile's products would wait
+          // for all loads in flight
+#pragma unroll
+          for (int u = 0; u < RT; ++u)
+#pragma unroll
+            for (int ii = 0; ii < 4; ++ii) asm volatile("" : "+v"(qf[u][ii]));
+          have_next = seg_end < x0 + nt;
+          if (have_next) load_q(c + __builtin_amdgcn_readfirstlane(seq_sh[seg_end - x0]), qn);
+#pragma unroll
+          for (int u = 0; u < RT; ++u) {
+            vis[u] = qi[u] >= 0 && qi[u] < blen ? m0 + qi[u] + 1 : 0;
+            m[u] = -INFINITY;
+            l[u] = 0.f;
+#pragma unroll
+            for (int mm = 0; mm < 8; ++mm) O[u][mm] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+          }
+        }
+        dead = dead || t.slot < 0;
+        if (dead) return;
+        // A tile below position m0 + 1 is inside the window of every valid query row and inside
+        // the context: no mask.  The rest (the causal diagonal and the partial tile at the end of
+        // the context) take the mask, which zeroes the V entries past the context in place.  Rows
+        // that are not valid queries (past the block, or padding) compute finite values nobody reads.
+        const int tb = 16 * (x - cb);
+        if (tb + 16 <= m0 + 1) attn_tiles<false, RT>(tb, L, g, a.scale_log2, t, qf, vis, m, l, O);
+        else attn_tiles<true, RT>(tb, L, g, a.scale_log2, t, qf, vis, m, l, O);
+      };
+      // The ring runs across segments: the loads of the next sequence's tiles are in flight while
+      // this one's last tiles are consumed.  The loads run unguarded in whole turns of the ring
+      // (one straight path, so every wait counts exactly the loads still in flight).
+      TileBuf ring[kAttnRing];
+#pragma unroll
+      for (int d = 0; d < kAttnRing - 1; ++d) load_tile(min(d, nt - 1), ring[d]);
+      for (int i = 0; i < nt; i += kAttnRing) {
+#pragma unroll
+        for (int d = 0; d < kAttnRing; ++d) {
+          // refill the buffer consumed last step (a re-read of the last tile near the end);
+          // the scheduling barriers keep each refill after the step that frees its buffer,
+          // so the ring keeps fixed registers and no copy waits on a load in flight
+          __builtin_amdgcn_sched_barrier(0);
+          load_tile(min(i + d + kAttnRing - 1, nt - 1), ring[(d + kAttnRing - 1) % kAttnRing]);
+          __builtin_amdgcn_sched_barrier(0);
+          step(i + d, ring[d]);
+        }
+      }
     }
   }
+  if (wave_ok) finish();   // the last segment
 }
 
 // Merge the partials of sequence b: the ranges that hold its tiles are parts
@@ -398,22 +461,24 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
 // time with every load issued before the first use, and merged in one pass.
 constexpr int kCombineBatch = 8;
 
-__global__ __launch_bounds__(256) void attn_combine_kernel(AttnK a, uint16_t *__restrict__ out) {
+__global__ __launch_bounds__(256) void attn_combine_kernel(AttnK a) {
   const int b = blockIdx.y;
   const int rows = a.G * a.R;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= a.n_kv * rows * 32) return;
   const int d = (idx & 31) * 4, r = (idx >> 5) % rows, kvh = (idx >> 5) / rows;
   const int hl = r / a.R, i = r % a.R;
+  const int TT = a.cum[a.B], cb = a.cum[b], T = a.cum[b + 1] - cb, P = a.parts;
+  int pf = 0, pl = 0;
+  if (T > 0) {
+    pf = min((int)(((long)(cb + 1) * P - 1) / TT), P - 1);
+    pl = min((int)(((long)(cb + T) * P - 1) / TT), P - 1);
+    if (part_begin(pf + 1, TT, P) >= cb + T) return;   // wholly in range pf, which has written its rows
+  }
   const int blen = block_rows(a.blen, a.blen_add, b, a.R);
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
   if (i < blen) {
-    const int TT = a.cum[a.B], cb = a.cum[b], T = a.cum[b + 1] - cb;
-    const int P = a.parts;
     if (T > 0) {
-      int pf = (int)(((long)(cb + 1) * P - 1) / TT), pl = (int)(((long)(cb + T) * P - 1) / TT);
-      pf = pf < P - 1 ? pf : P - 1;
-      pl = pl < P - 1 ? pl : P - 1;
       float M = -INFINITY, den = 0.f;
       float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
       for (int p0 = pf; p0 <= pl; p0 += kCombineBatch) {
@@ -448,7 +513,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnK a, uint16_t *__
   }
   const uint2 packed = make_uint2(f32_to_bf16(v.x) | (uint32_t(f32_to_bf16(v.y)) << 16),
                                   f32_to_bf16(v.z) | (uint32_t(f32_to_bf16(v.w)) << 16));
-  *reinterpret_cast<uint2 *>(out + (((long)b * a.R + i) * a.n_heads + kvh * a.G + hl) * 128 + d) = packed;
+  *reinterpret_cast<uint2 *>(a.out + (((long)b * a.R + i) * a.n_heads + kvh * a.G + hl) * 128 + d) = packed;
 }
 
 // ------------------------------------------------------------------ float32 path
@@ -680,6 +745,7 @@ void run_attention(const AttnArgs &a, const AttnPlan &p, char *ws, hipStream_t s
     k.base = a.base_lens;
     k.blen = a.blk_len;
     k.q = (const uint16_t *)a.q;
+    k.out = (uint16_t *)a.out;
     k.part_o = (float *)(ws + p.part_o);
     k.part_ml = (float2 *)(ws + p.part_ml);
     k.cum = (int32_t *)(ws + p.cum);
@@ -712,7 +778,7 @@ void run_attention(const AttnArgs &a, const AttnPlan &p, char *ws, hipStream_t s
     }
     TraceScope ts(a.trace_combine, s);
     const int items = a.n_kv * G * a.R * 32;
-    hipLaunchKernelGGL(attn_combine_kernel, dim3((items + 255) / 256, a.B), dim3(256), 0, s, k, (uint16_t *)a.out);
+    hipLaunchKernelGGL(attn_combine_kernel, dim3((items + 255) / 256, a.B), dim3(256), 0, s, k);
   } else {
     AttnF f{};
     f.kp = (const float *)a.k_pages;

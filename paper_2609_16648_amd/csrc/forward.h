@@ -8,7 +8,7 @@ namespace gm {
 
 constexpr int kMaxRowFloats = 16384;   // float32 row that the row kernels stage in LDS (64 KiB)
 constexpr int kAttnMaxRows = 64;   // (n_heads / n_kv_heads) * block rows per KV head
-constexpr int kAttnWinPages = 256; // page ids that a workgroup of the attention holds in LDS at a time
+constexpr int kAttnWinTiles = 256;   // 16-token tiles whose places a workgroup of the attention holds in LDS at a time
 
 struct Carve {
   size_t off = 0;
