@@ -66,9 +66,11 @@ __device__ __forceinline__ int block_rows(const int32_t *blen, int add, int b, i
   return n < 0 ? 0 : (n > R ? R : n);
 }
 
-// 16-token tiles of sequence b: its context is base + base_off + valid block rows
-__device__ __forceinline__ int seq_tiles(const AttnK &a, int b) {
-  const int L = a.base[b] + a.base_off + block_rows(a.blen, a.blen_add, b, a.R);
+// 16-token tiles of sequence b: its context is its block's start m0 plus its valid block rows
+__device__ __forceinline__ int seq_tiles(const AttnK &a, int b, int &m0, int &rows) {
+  m0 = a.base[b] + a.base_off;
+  rows = block_rows(a.blen, a.blen_add, b, a.R);
+  const int L = m0 + rows;
   return L > 0 ? (L + 15) >> 4 : 0;
 }
 
@@ -228,14 +230,14 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
   const int tid = threadIdx.x, nthr = blockDim.x;
   const bool one_chunk = a.B <= nthr;   // a batch that fits one block needs a single scan
   const bool writer = part == 0 && grp == 0;
-  int TT = 0, T1 = 0, cb1 = 0;
+  int TT = 0, T1 = 0, cb1 = 0, m1 = 0, r1 = 0;   // this thread's sequence of the chunk
   if (one_chunk) {
-    T1 = tid < a.B ? seq_tiles(a, tid) : 0;
+    T1 = tid < a.B ? seq_tiles(a, tid, m1, r1) : 0;
     cb1 = block_excl_scan(T1, scan_sh, &TT);
     if (writer && tid < a.B) a.cum[tid] = cb1;
   } else {
     for (int c = 0; c < a.B; c += nthr) {
-      const int T = c + tid < a.B ? seq_tiles(a, c + tid) : 0;
+      const int T = c + tid < a.B ? seq_tiles(a, c + tid, m1, r1) : 0;
       int tot;
       const int cb = TT + block_excl_scan(T, scan_sh, &tot);
       if (writer && c + tid < a.B) a.cum[c + tid] = cb;
@@ -269,7 +271,7 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
   // start, context, tiles before the sequence and up to its end, end of the segment; the queries, the softmax state, and the
   // queries of the next segment, loaded one segment ahead.
   int b = -1, m0 = 0, L = 0, cb = 0, seq_end = 0, seg_end = s;
-  bool dead = false, have_next = false;
+  bool dead = false;
   bf16x8_t qf[RT][4], qn[RT][4];
   int vis[RT];
   float m[RT], l[RT];
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
       cbt = cb1;
       tot = TT;
     } else {
-      T = c + tid < a.B ? seq_tiles(a, c + tid) : 0;
+      T = c + tid < a.B ? seq_tiles(a, c + tid, m1, r1) : 0;
       cbt = run + block_excl_scan(T, scan_sh, &tot);
     }
     const int cbeg = run, cend = run + tot;
@@ -345,10 +347,8 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
     __syncthreads();   // the previous chunk's tables are read
     cum_sh[tid] = cbt;
     if (tid == 0) cum_sh[nthr] = cend;
-    if (T > 0) {
-      m0_sh[tid] = a.base[c + tid] + a.base_off;
-      bl_sh[tid] = block_rows(a.blen, a.blen_add, c + tid, a.R);
-    }
+    m0_sh[tid] = m1;
+    bl_sh[tid] = r1;
     const int xe = min(e, cend);
     for (int x0 = max(s, cbeg); x0 < xe; x0 += kAttnWinTiles) {
       const int nt = min(kAttnWinTiles, xe - x0);
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
       // outside the pool is reported; it ends its segment before its first token.
       __syncthreads();
       for (int i = tid; i < nt; i += nthr) {
-        int lo = 0, hi = nthr;   // the last sequence with at most x0 + i tiles before it
+        int lo = 0, hi = min(nthr, a.B - c);   // the last sequence with at most x0 + i tiles before it
         while (hi - lo > 1) {
           const int mid = (lo + hi) >> 1;
           if (cum_sh[mid] <= x0 + i) lo = mid;
@@ -396,22 +396,17 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
           seq_end = __builtin_amdgcn_readfirstlane(cum_sh[q + 1]);
           seg_end = min(e, seq_end);
           dead = false;
-          if (have_next) {
 #pragma unroll
-            for (int u = 0; u < RT; ++u)
+          for (int u = 0; u < RT; ++u)
 #pragma unroll
-              for (int ii = 0; ii < 4; ++ii) qf[u][ii] = qn[u][ii];
-          } else {
-            load_q(b, qf);
-          }
+            for (int ii = 0; ii < 4; ++ii) qf[u][ii] = qn[u][ii];
           // the queries have arrived before the paths join, or every tile's products would wait
           // for all loads in flight
 #pragma unroll
           for (int u = 0; u < RT; ++u)
 #pragma unroll
             for (int ii = 0; ii < 4; ++ii) asm volatile("" : "+v"(qf[u][ii]));
-          have_next = seg_end < x0 + nt;
-          if (have_next) load_q(c + __builtin_amdgcn_readfirstlane(seq_sh[seg_end - x0]), qn);
+          if (seg_end < x0 + nt) load_q(c + __builtin_amdgcn_readfirstlane(seq_sh[seg_end - x0]), qn);
 #pragma unroll
           for (int u = 0; u < RT; ++u) {
             vis[u] = qi[u] >= 0 && qi[u] < blen ? m0 + qi[u] + 1 : 0;
@@ -435,6 +430,8 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
       // this one's last tiles are consumed.  The loads run unguarded in whole turns of the ring
       // (one straight path, so every wait counts exactly the loads still in flight).
       TileBuf ring[kAttnRing];
+      // the queries of the first segment that begins in this window
+      if (seg_end < x0 + nt) load_q(c + __builtin_amdgcn_readfirstlane(seq_sh[seg_end - x0]), qn);
 #pragma unroll
       for (int d = 0; d < kAttnRing - 1; ++d) load_tile(min(d, nt - 1), ring[d]);
       for (int i = 0; i < nt; i += kAttnRing) {
@@ -456,16 +453,21 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
 
 // Merge the partials of sequence b: the ranges that hold its tiles are parts
 // p_first .. p_last (empty ranges among them wrote nothing and are skipped);
-// the partial of (part p, sequence b) sits in slot p + b.  One thread per
-// (KV head, row, four channels); the partials are read kCombineBatch at a
-// time with every load issued before the first use, and merged in one pass.
+// the partial of (part p, sequence b) sits in slot p + b.  A thread per (KV head,
+// row, four channels) reads partials kCombineBatch at a time with every load issued
+// before the first use, and merges them in one pass.  SP groups of 32 threads share a
+// row, group i taking batches i, i + SP, ..; their results meet in LDS in group order.
+// SP = 16 where few sequences are cut into many partials each: the pass is a chain of
+// load round trips (one sequence in 126 partials: 42 us with one group, 8.5 with sixteen).
 constexpr int kCombineBatch = 8;
 
-__global__ __launch_bounds__(256) void attn_combine_kernel(AttnK a) {
+template <int SP>
+__global__ __launch_bounds__(SP > 1 ? 32 * SP : 256) void attn_combine_kernel(AttnK a) {
   const int b = blockIdx.y;
   const int rows = a.G * a.R;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= a.n_kv * rows * 32) return;
+  const int tid = threadIdx.x, sp = SP > 1 ? tid >> 5 : 0;
+  const int idx = SP > 1 ? blockIdx.x * 32 + (tid & 31) : blockIdx.x * blockDim.x + tid;
+  if (idx >= a.n_kv * rows * 32) return;   // (SP > 1: a block per row, never taken)
   const int d = (idx & 31) * 4, r = (idx >> 5) % rows, kvh = (idx >> 5) / rows;
   const int hl = r / a.R, i = r % a.R;
   const int TT = a.cum[a.B], cb = a.cum[b], T = a.cum[b + 1] - cb, P = a.parts;
@@ -476,40 +478,56 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnK a) {
     if (part_begin(pf + 1, TT, P) >= cb + T) return;   // wholly in range pf, which has written its rows
   }
   const int blen = block_rows(a.blen, a.blen_add, b, a.R);
-  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (i < blen) {
-    if (T > 0) {
-      float M = -INFINITY, den = 0.f;
-      float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int p0 = pf; p0 <= pl; p0 += kCombineBatch) {
-        float2 ml[kCombineBatch];
-        float4 o[kCombineBatch];
+  float M = -INFINITY, den = 0.f;
+  float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto merge = [&](float m2, float l2, float4 o2) {
+    const float mn = fmaxf(M, m2);
+    const float sc = __builtin_amdgcn_exp2f(M - mn), w = __builtin_amdgcn_exp2f(m2 - mn);   // M = -inf: sc = 0
+    den = den * sc + l2 * w;
+    num.x = num.x * sc + o2.x * w;
+    num.y = num.y * sc + o2.y * w;
+    num.z = num.z * sc + o2.z * w;
+    num.w = num.w * sc + o2.w * w;
+    M = mn;
+  };
+  if (i < blen && T > 0) {
+    for (int p0 = pf + kCombineBatch * sp; p0 <= pl; p0 += kCombineBatch * SP) {
+      float2 ml[kCombineBatch];
+      float4 o[kCombineBatch];
 #pragma unroll
-        for (int u = 0; u < kCombineBatch; ++u) {
-          const int p = min(p0 + u, pl);
-          const long pr = ((long)(p + b) * a.n_kv + kvh) * a.rows_pad + r;
-          ml[u] = a.part_ml[pr];
-          o[u] = *reinterpret_cast<const float4 *>(a.part_o + pr * 128 + d);
-        }
-#pragma unroll
-        for (int u = 0; u < kCombineBatch; ++u) {
-          const int p = p0 + u;
-          if (p > pl || part_begin(p, TT, P) == part_begin(p + 1, TT, P) || ml[u].x == -INFINITY) continue;
-          const float mn = fmaxf(M, ml[u].x);
-          const float sc = __builtin_amdgcn_exp2f(M - mn), w = __builtin_amdgcn_exp2f(ml[u].x - mn);   // M = -inf: sc = 0
-          den = den * sc + ml[u].y * w;
-          num.x = num.x * sc + o[u].x * w;
-          num.y = num.y * sc + o[u].y * w;
-          num.z = num.z * sc + o[u].z * w;
-          num.w = num.w * sc + o[u].w * w;
-          M = mn;
-        }
+      for (int u = 0; u < kCombineBatch; ++u) {
+        const int p = min(p0 + u, pl);
+        const long pr = ((long)(p + b) * a.n_kv + kvh) * a.rows_pad + r;
+        ml[u] = a.part_ml[pr];
+        o[u] = *reinterpret_cast<const float4 *>(a.part_o + pr * 128 + d);
       }
-      if (M != -INFINITY) {
-        const float inv = 1.f / den;
-        v = make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv);
+#pragma unroll
+      for (int u = 0; u < kCombineBatch; ++u) {
+        const int p = p0 + u;
+        if (p > pl || part_begin(p, TT, P) == part_begin(p + 1, TT, P) || ml[u].x == -INFINITY) continue;
+        merge(ml[u].x, ml[u].y, o[u]);
       }
     }
+  }
+  if constexpr (SP > 1) {
+    __shared__ float sh[SP][6][32];
+    const int c = tid & 31;
+    sh[sp][0][c] = M;
+    sh[sp][1][c] = den;
+    sh[sp][2][c] = num.x;
+    sh[sp][3][c] = num.y;
+    sh[sp][4][c] = num.z;
+    sh[sp][5][c] = num.w;
+    __syncthreads();
+    if (sp) return;
+#pragma unroll
+    for (int u = 1; u < SP; ++u)
+      if (sh[u][0][c] != -INFINITY) merge(sh[u][0][c], sh[u][1][c], make_float4(sh[u][2][c], sh[u][3][c], sh[u][4][c], sh[u][5][c]));
+  }
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (M != -INFINITY) {
+    const float inv = 1.f / den;
+    v = make_float4(num.x * inv, num.y * inv, num.z * inv, num.w * inv);
   }
   const uint2 packed = make_uint2(f32_to_bf16(v.x) | (uint32_t(f32_to_bf16(v.y)) << 16),
                                   f32_to_bf16(v.z) | (uint32_t(f32_to_bf16(v.w)) << 16));
@@ -777,8 +795,14 @@ void run_attention(const AttnArgs &a, const AttnPlan &p, char *ws, hipStream_t s
         hipLaunchKernelGGL((attn_mfma_kernel<false, 2>), grid, block, kAttnLdsReserve, s, k);
     }
     TraceScope ts(a.trace_combine, s);
-    const int items = a.n_kv * G * a.R * 32;
-    hipLaunchKernelGGL(attn_combine_kernel, dim3((items + 255) / 256, a.B), dim3(256), 0, s, k);
+    const int out_rows = a.n_kv * G * a.R;
+    // more than a batch of partials per sequence, and few enough rows that a workgroup for each costs
+    // less than the round trips it saves (one row per sequence: 7 sequences in 18 partials each 13.6 ->
+    // 7.6 us; 16 sequences of 128 rows in 8 partials: 14 us slower with a workgroup per row)
+    if (p.parts >= 8 * a.B && (long)out_rows * a.B <= 512)
+      hipLaunchKernelGGL(attn_combine_kernel<16>, dim3(out_rows, a.B), dim3(512), 0, s, k);
+    else
+      hipLaunchKernelGGL(attn_combine_kernel<1>, dim3((out_rows + 7) / 8, a.B), dim3(256), 0, s, k);
   } else {
     AttnF f{};
     f.kp = (const float *)a.k_pages;

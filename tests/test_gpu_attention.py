@@ -76,6 +76,27 @@ def test_bf16_attention_many_sequences(lens, k, page_size):
     assert np.abs(got - oracle.round_bf16(ref)).max() <= 2.0 ** -7 * np.abs(ref).max()
 
 
+def test_bf16_attention_sequences_after_a_window():
+    # 40 KV heads: ten head groups, so a range holds more tiles than a window of the page list; the
+    # short sequences begin in the later windows of a range, behind a sequence that began before them
+    need_gpu()
+    shape = dataclasses.replace(synth.QWEN3_4B_LAYER, n_heads=40, n_kv_heads=40)
+    lens, k = np.array([60000, 300, 50000, 17, 40]), 1
+    cache = gm.PagedCache(shape, 1, lens, lens + k + 1, page_size=16, seed=3, fill="empty")
+    for t in cache.k + cache.v:
+        t.normal_(generator=torch.Generator(device="cuda").manual_seed(5))
+    q = synth.normal_tensor((len(lens), k + 1, 40, 128), 5, "bf16", "q-window")
+    out = torch.empty(q.shape, dtype=torch.bfloat16, device="cuda")
+    gm.verify_attention(gm.model_config(shape), cache, 0, t32(q, torch.bfloat16), out, gm.Workspace())
+    torch.cuda.synchronize()
+    for b in (1, 3, 4):
+        kk, vv = cache.read(0, b, np.arange(lens[b] + k + 1))
+        ref = oracle.attention(q[b].astype(np.float64), kk.astype(np.float64), vv.astype(np.float64),
+                               lens[b] + np.arange(k + 1) + 1)
+        got = out[b].float().cpu().numpy()
+        assert np.abs(got - oracle.round_bf16(ref)).max() <= 2.0 ** -7 * np.abs(ref).max(), b
+
+
 def test_f32_attention_matches_oracle():
     need_gpu()
     shape = synth.TINY
