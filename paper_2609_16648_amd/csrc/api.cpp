@@ -212,30 +212,30 @@ gm_status spec_accept_impl(int B, int k, int V, int mode, float temperature, flo
   } else {
     launch_row_stats("accept_row_stats", target_logits, V, B * (k + 1), V, inv_t, tstat, s, submax);
   }
+  // top-p (sample mode): the nuclei of every target and draft row, each right after the pass over
+  // the same rows, while the last-level cache still holds them
+  const bool top_p_on = mode == GM_SAMPLE && top_p < 1.f;
+  const double inv_td = 1.0 / (double)temperature;
+  NucRow *tnuc = nullptr, *dnuc = nullptr;
+  unsigned long long *part = (unsigned long long *)(w + p.nucpart);
+  if (top_p_on) {
+    tnuc = (NucRow *)(w + p.tnuc);
+    launch_nucleus("accept_nucleus", B * (k + 1), V, inv_td, (double)top_p, target_logits, V, tstat, nch_t,
+                   tnuc, 1, part, s);
+  }
   // q's statistics: the draft head's own (one per row) when the caller has them, else a pass over the rows
   int nch_d = stat_chunks(V);
-  const bool top_p_on = mode == GM_SAMPLE && top_p < 1.f;
   if (mode == GM_SAMPLE && k > 0) {
     if (top_p_on && draft_nucleus) {
       nch_d = 0;                      // the draft rows' nuclei carry their reference and mass
+      dnuc = (NucRow *)draft_nucleus;
     } else if (draft_stats) {
       dstat = (RowStat *)draft_stats;
       nch_d = 1;
     } else {
       launch_row_stats("accept_row_stats", draft_logits, V, B * k, V, inv_t, dstat, s);
     }
-  }
-  // top-p (sample mode): the nuclei of every target and draft row
-  const double inv_td = 1.0 / (double)temperature;
-  NucRow *tnuc = nullptr, *dnuc = nullptr;
-  if (top_p_on) {
-    tnuc = (NucRow *)(w + p.tnuc);
-    unsigned long long *part = (unsigned long long *)(w + p.nucpart);
-    launch_nucleus("accept_nucleus", B * (k + 1), V, inv_td, (double)top_p, target_logits, V, tstat, nch_t,
-                   tnuc, 1, part, s);
-    if (k > 0 && draft_nucleus) {
-      dnuc = (NucRow *)draft_nucleus;
-    } else if (k > 0) {
+    if (top_p_on && !draft_nucleus) {
       dnuc = (NucRow *)(w + p.dnuc);
       launch_nucleus("accept_nucleus", B * k, V, inv_td, (double)top_p, draft_logits, V, dstat, nch_d, dnuc, 1, part,
                      s);

@@ -124,7 +124,7 @@ void launch_accept_decide(int B, int k, int V, int mode, float inv_t, double inv
 // statistics (chunks or tiles) at st + r * nch, into out[r * out_stride]; 0 < top_p < 1.  part (may be null):
 // kNucPartBytes of scratch that lets launches of few rows split their first pass
 constexpr int kNucSplitRows = 256;     // rows x workgroups per row of a split first pass
-constexpr int kNucMaxSplit = 8;
+constexpr int kNucMaxSplit = 16;
 constexpr size_t kNucPartBytes = (size_t)kNucSplitRows * 4096 * 8;
 void launch_nucleus(const char *name, int n_rows, int V, double inv_td, double top_p, const float *logits,
                     long row_stride, const RowStat *st, int nch, NucRow *out, int out_stride,

@@ -585,47 +585,65 @@ void launch_record_topk(int B, int k, int V, float inv_t, int topk, const float 
 // gathers the logits and ids of the boundary's 12-bit bin into LDS; the finer
 // bins and the ties are then taken from there (a bin too large for LDS takes
 // passes over the row instead).
+//  Peaked rows, the common case of a language model, need one pass and no histogram
+// atomics over the row: a pass sums every id's mass in registers and queues the few
+// ids likely enough to reach the boundary; if the queue's mass reaches top_p of the
+// row's, the boundary is among them.  Otherwise, and for flat rows, the passes above
+// run.  Both find the same boundary from the same integers.
 constexpr int kNucThreads = 1024;
 constexpr int kNucBins = 4096;
 constexpr int kNucQueue = 12288;     // logits and ids of the boundary's 12-bit bin kept in LDS (96 KiB)
 constexpr int kNucTieRank = 2048;    // ties at the boundary ranked in LDS (more: a pass over the row)
+// A row is peaked when its likeliest id holds at least 1 / kNucFlat of the mass (flat rows,
+// e.g. 1.5e5 N(0, 1) logits, put 1 / 3000 there, and their nucleus holds a third of the ids).
+// The queued ids are those above (1 - top_p) / kNucTail of the mass: fewer than kNucTail ids
+// between that and the boundary cannot hide it.  Both only choose the path.
+constexpr double kNucFlat = 64.0;
+constexpr double kNucTail = 2048.0;
+constexpr int kNucRank = 256;        // queued ids ranked by counting (more: the radix selection over the queue)
+constexpr int kNucSliceMax = kNucBins - 2;   // ids queued by one slice of a split pass
 
-// exp(y) for -32 <= y <= 0 by Tang's table-driven reduction (ACM TOMS 15(2), 1989):
-// y = (64 q + j) ln2 / 64 + r with |r| <= ln2 / 128, exp(y) = 2^q 2^(j/64) exp(r), and
-// exp(r) by its Taylor polynomial to r^6 (truncation below 2^-64 at |r| <= ln2 / 128).
-// ln2 / 64 is split into a 32-bit head (k times it is exact for |k| < 2^21) and a tail;
-// tab[j] = 2^(j/64), filled per block (nuc_exp_table).  A few ulps in all, far below
-// the 2^-44 units the masses are rounded to.
-__device__ __forceinline__ double nuc_exp(double y, const double *tab) {
-  constexpr double kLn2Hi = 0x1.62e42feep-1 / 64.0, kLn2Lo = 0x1.a39ef35793c76p-33 / 64.0;
-  const double kd = rint(y * (64.0 / 0x1.62e42fefa39efp-1));
+// exp(y) 2^44 for -32 <= y <= 0 by Tang's table-driven reduction (ACM TOMS 15(2), 1989):
+// y = (kNucTab q + j) ln2 / kNucTab + r with |r| <= ln2 / (2 kNucTab) = 1.7e-4, exp(y) = 2^q
+// 2^(j/kNucTab) exp(r), and exp(r) by its Taylor polynomial to r^3 (truncation below 2^-54).
+// ln2 / kNucTab is split into a 32-bit head (k times it is exact for |k| < 2^21) and a tail;
+// tab[j] = 2^(44 + j/kNucTab), filled per block (nuc_exp_table); q goes into the exponent
+// bits.  A few ulps in all, far below the unit that the masses are rounded to.  (64 entries
+// and a polynomial to r^6 took three more float64 multiply-adds per id.)
+constexpr int kNucTab = 2048;
+__device__ __forceinline__ double nuc_exp44(double y, const double *tab) {
+  constexpr double kLn2Hi = 0x1.62e42feep-1 / kNucTab, kLn2Lo = 0x1.a39ef35793c76p-33 / kNucTab;
+  const double kd = rint(y * (kNucTab / 0x1.62e42fefa39efp-1));
   double r = fma(-kd, kLn2Hi, y);
   r = fma(-kd, kLn2Lo, r);
-  double p = 1.0 / 720.0;
-  p = fma(p, r, 1.0 / 120.0);
-  p = fma(p, r, 1.0 / 24.0);
-  p = fma(p, r, 1.0 / 6.0);
-  p = fma(p, r, 0.5);
+  double p = fma(r, 1.0 / 6.0, 0.5);
   p = fma(p, r, 1.0);
   p = fma(p, r, 1.0);
   const int k = (int)kd;
-  return ldexp(tab[k & 63] * p, k >> 6);
+  const long long t = __double_as_longlong(tab[k & (kNucTab - 1)] * p);   // in [2^44, 2^45]
+  return __longlong_as_double(t + ((long long)(k >> 11) << 52));           // 2^q, q >= -47: stays normal
 }
+static_assert(kNucTab == 1 << 11, "nuc_exp44 shifts by log2 of the table size");
 
-// the block's table of 2^(j/64), j = 0..63 (before the block's first barrier)
+// the block's table (before the block's first barrier)
 __device__ __forceinline__ void nuc_exp_table(double *tab) {
-  if (threadIdx.x < 64) tab[threadIdx.x] = exp2((double)threadIdx.x / 64.0);
+  for (int j = threadIdx.x; j < kNucTab; j += blockDim.x) tab[j] = exp2(44.0 + (double)j / kNucTab);
 }
 
-// mass of one id in 2^-44 units (the same operations at every call: no contraction)
-__device__ __forceinline__ unsigned long long nuc_mass(float v, double inv_td, double m, const double *tab) {
+// mass of one id in 2^-44 units (the same operations at every call: no contraction); y gets
+// its exponent z / T - m
+__device__ __forceinline__ unsigned long long nuc_mass(float v, double inv_td, double m, const double *tab, double &y) {
 #pragma clang fp contract(off)
-  const double y = (double)v * inv_td - m;
+  y = (double)v * inv_td - m;
   if (!(y >= -32.0)) return 0ull;          // exp(-32) 2^44 < 0.5: rounds to 0 (and -inf, NaN)
   // exp(y) 2^44 < 2^52: adding 2^52 leaves its nearest integer (ties to even) in the
   // low mantissa bits
-  const double t = nuc_exp(y, tab) * 0x1p44 + 0x1p52;
+  const double t = nuc_exp44(y, tab) + 0x1p52;
   return (unsigned long long)(__double_as_longlong(t) - 0x4330000000000000ll);
+}
+__device__ __forceinline__ unsigned long long nuc_mass(float v, double inv_td, double m, const double *tab) {
+  double y;
+  return nuc_mass(v, inv_td, m, tab, y);
 }
 
 __device__ __forceinline__ float key_value(uint32_t k) {   // inverse of order_key
@@ -717,10 +735,11 @@ __device__ __forceinline__ void nuc_visit(const float *__restrict__ row, int V, 
 }
 
 // The reference exponent of a row: z / T (float64) of its maximum, the lowest id
-// attaining the largest statistic among its nch chunk or tile statistics.  Holds a
-// barrier: the caller's LDS writes before it are visible to the block after it.
+// attaining the largest statistic among its nch chunk or tile statistics; S gets the
+// row's mass relative to it, from the statistics (the same in every block that asks).
+// Holds barriers: the caller's LDS writes before it are visible to the block after it.
 __device__ double nuc_reference(const float *__restrict__ row, const RowStat *__restrict__ st, int nch, int V,
-                                double inv_td, float *red_m, int *red_a) {
+                                double inv_td, float *red_m, int *red_a, double *red_s, double &S) {
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   float bm = -INFINITY;
   int ba = 0x7fffffff;
@@ -753,34 +772,87 @@ __device__ double nuc_reference(const float *__restrict__ row, const RowStat *__
       ba = red_a[w];
     }
   if (ba < 0 || ba >= V) ba = 0;
-  return (double)row[ba] * inv_td;
+  const double ref = (double)row[ba] * inv_td;
+  double part = 0.0;
+  for (int c = tid; c < nch; c += kNucThreads) part += st[c].sum * exp((double)st[c].max - (double)bm);
+  part = wave_sum(part);
+  if (lane == 0) red_s[wid] = part;
+  __syncthreads();
+  S = 0.0;
+  for (int w = 0; w < kNucThreads / 64; ++w) S += red_s[w];
+  return ref;
+}
+
+// whether the row takes the queue, and the exponent from which its ids are queued
+__device__ __forceinline__ bool nuc_peaked(double S) { return S >= 0.5 && S <= kNucFlat; }
+__device__ __forceinline__ double nuc_cut(double S, double top_p) {
+  const double c = log(S * (1.0 - top_p) / kNucTail);
+  return c > -32.0 ? c : -32.0;
+}
+
+// sum of one value per thread over the block; wtot >= 16 entries.  Holds barriers.
+__device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v, unsigned long long *wtot) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) wtot[threadIdx.x >> 6] = v;
+  __syncthreads();
+  unsigned long long t = 0;
+  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += wtot[w];
+  return t;
 }
 
 // Pass 1 of the selection split over S workgroups per row, for launches with too
-// few rows to fill the chip: workgroup (r, s) writes the histogram of its slice of
-// row r (ids [lo, hi), lo and hi multiples of 4) to part[(r S + s) kNucBins ...];
-// the selection sums the S of them (exact integers: the same result as one pass).
-__global__ __launch_bounds__(kNucThreads) void nucleus_hist_kernel(int V, double inv_td,
+// few rows to fill the chip: workgroup (r, s) takes its slice of row r (ids [lo, hi),
+// lo and hi multiples of 4) to part[(r S + s) kNucBins ...].  Flat rows: the slice's
+// histogram; the selection sums the S of them (exact integers: the same result as one
+// pass).  Peaked rows: the slice's mass, the number of its ids past the cut, and those
+// ids (logit bits in the upper half), up to kNucSliceMax of them.
+__global__ __launch_bounds__(kNucThreads) void nucleus_hist_kernel(int V, double inv_td, double top_p,
                                                                    const float *__restrict__ logits, long row_stride,
                                                                    const RowStat *__restrict__ st, int nch, int S,
                                                                    unsigned long long *__restrict__ part) {
   __shared__ unsigned long long hist[kNucBins];
   __shared__ float red_m[kNucThreads / 64];
   __shared__ int red_a[kNucThreads / 64];
-  __shared__ double etab[64];
+  __shared__ double red_s[kNucThreads / 64];
+  __shared__ unsigned long long wtot[kNucThreads / 64];
+  __shared__ double etab[kNucTab];
+  __shared__ unsigned sh_qn;
   const int r = blockIdx.x / S, sg = blockIdx.x % S, tid = threadIdx.x;
   const float *row = logits + (long)r * row_stride;
   nuc_exp_table(etab);
   for (int b = tid; b < kNucBins; b += kNucThreads) hist[b] = 0ull;
-  const double m = nuc_reference(row, st + (long)r * nch, nch, V, inv_td, red_m, red_a);
+  if (tid == 0) sh_qn = 0u;
+  double mass;
+  const double m = nuc_reference(row, st + (long)r * nch, nch, V, inv_td, red_m, red_a, red_s, mass);
   const int lo = (int)(((long)V * sg / S) & ~3l), hi = sg + 1 == S ? V : (int)(((long)V * (sg + 1) / S) & ~3l);
   const bool vec = (V & 3) == 0 && (row_stride & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
+  unsigned long long *dst = part + ((long)r * S + sg) * kNucBins;
+  if (nuc_peaked(mass)) {
+    const double cut = nuc_cut(mass, top_p);
+    unsigned long long t = 0;
+    nuc_visit(row + lo, hi - lo, vec, [&](float v, int x) {
+      double y;
+      t += nuc_mass(v, inv_td, m, etab, y);
+      if (y >= cut) {
+        const unsigned slot = atomicAdd(&sh_qn, 1u);
+        if (slot < (unsigned)kNucSliceMax)
+          dst[2 + slot] = ((unsigned long long)__float_as_uint(v) << 32) | (unsigned)(lo + x);
+      }
+    });
+    t = block_sum_u64(t, wtot);
+    if (tid == 0) {
+      dst[0] = t;
+      dst[1] = sh_qn;
+    }
+    return;
+  }
   nuc_visit(row + lo, hi - lo, vec, [&](float v, int) {
     const unsigned long long e = nuc_mass(v, inv_td, m, etab);
     if (e) atomicAdd(&hist[order_key(v) >> 20], e);
   });
   __syncthreads();
-  unsigned long long *dst = part + ((long)r * S + sg) * kNucBins;
   for (int b = tid; b < kNucBins; b += kNucThreads) dst[b] = hist[b];
 }
 
@@ -798,73 +870,141 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
   __shared__ int red_a[kNucThreads / 64];
   __shared__ int sh_bin, sh_idt;
   __shared__ unsigned long long sh_above;
-  __shared__ double etab[64];
-  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  __shared__ double red_s[kNucThreads / 64];
+  __shared__ double etab[kNucTab];
+  const int r = blockIdx.x, tid = threadIdx.x;
   const float *row = logits + (long)r * row_stride;
 
   nuc_exp_table(etab);
   for (int b = tid; b < kNucBins; b += kNucThreads) hist[b] = 0ull;
-  const double m = nuc_reference(row, st + (long)r * nch, nch, V, inv_td, red_m, red_a);
-
-  // pass 1: the top 12 bits of the key (or the sum of the S slices' histograms)
+  if (tid == 0) sh_qn = 0u;
+  double S_row;
+  const double m = nuc_reference(row, st + (long)r * nch, nch, V, inv_td, red_m, red_a, red_s, S_row);
   const bool vec = (V & 3) == 0 && (row_stride & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
-  if (part) {
-    const unsigned long long *src = part + (long)r * S * kNucBins;
-    for (int b = tid; b < kNucBins; b += kNucThreads) {
-      unsigned long long t = 0;
-      for (int sg = 0; sg < S; ++sg) t += src[(long)sg * kNucBins + b];
-      hist[b] = t;
+  const bool peaked = nuc_peaked(S_row);
+  auto push = [&](float v, int x) {
+    const unsigned slot = atomicAdd(&sh_qn, 1u);
+    if (slot < (unsigned)kNucQueue) {
+      qv[slot] = v;
+      qx[slot] = x;
     }
-  } else {
-    nuc_visit(row, V, vec, [&](float v, int) {
-      const unsigned long long e = nuc_mass(v, inv_td, m, etab);
-      if (e) atomicAdd(&hist[order_key(v) >> 20], e);
-    });
+  };
+
+  unsigned long long tot = 0, above = 0;
+  double thr = 0.0;
+  unsigned qn = 0;
+  bool queued = false;   // the boundary is among the queued ids
+  if (peaked) {
+    unsigned long long t = 0;
+    if (part) {
+      const unsigned long long *src = part + (long)r * S * kNucBins;
+      for (int sg = 0; sg < S; ++sg) {
+        const unsigned long long n = src[(long)sg * kNucBins + 1];
+        if (tid == 0) {
+          t += src[(long)sg * kNucBins];
+          if (n > kNucSliceMax) atomicAdd(&sh_qn, (unsigned)kNucQueue + 1u);   // ids are missing: not queued
+        }
+        for (unsigned i = tid; i < (unsigned)n && i < (unsigned)kNucSliceMax; i += kNucThreads) {
+          const unsigned long long c = src[(long)sg * kNucBins + 2 + i];
+          push(__uint_as_float((uint32_t)(c >> 32)), (int)(uint32_t)c);
+        }
+      }
+    } else {
+      const double cut = nuc_cut(S_row, top_p);
+      nuc_visit(row, V, vec, [&](float v, int x) {
+        double y;
+        t += nuc_mass(v, inv_td, m, etab, y);
+        if (y >= cut) push(v, x);
+      });
+    }
+    tot = block_sum_u64(t, wtot);
+    thr = top_p * (double)tot;
+    qn = sh_qn;
+    if (qn <= (unsigned)kNucQueue) {
+      unsigned long long q = 0;
+      for (unsigned i = tid; i < qn; i += kNucThreads) q += nuc_mass(qv[i], inv_td, m, etab);
+      q = block_sum_u64(q, wtot);
+      queued = tot > 0 && (double)q >= thr;
+    }
+    if (queued && qn <= (unsigned)kNucRank) {
+      // few: each id's running mass is the mass of the ids ranked before it; the boundary is the
+      // id whose own mass takes it to thr, and the ids of equal logit past it are left out
+      unsigned long long *qm = hist;
+      for (unsigned i = tid; i < qn; i += kNucThreads) qm[i] = nuc_mass(qv[i], inv_td, m, etab);
+      __syncthreads();
+      for (unsigned i = tid; i < qn; i += kNucThreads) {
+        const uint32_t k = order_key(qv[i]);
+        const int x = qx[i];
+        unsigned long long before = 0;
+        bool more = false;
+        for (unsigned j = 0; j < qn; ++j) {
+          const uint32_t kj = order_key(qv[j]);
+          const bool first = kj > k || (kj == k && qx[j] < x);
+          before += first ? qm[j] : 0ull;
+          more = more || (kj == k && qx[j] > x);
+        }
+        if ((double)before < thr && (double)(before + qm[i]) >= thr)
+          out[(long)r * out_stride] = NucRow{m, (double)(before + qm[i]) * 0x1p-44, k, more ? x : 0x7fffffff};
+      }
+      return;
+    }
+    __syncthreads();
+    if (queued) {
+      for (unsigned i = tid; i < qn; i += kNucThreads)
+        atomicAdd(&hist[order_key(qv[i]) >> 20], nuc_mass(qv[i], inv_td, m, etab));
+      __syncthreads();
+    }
   }
-  __syncthreads();
-  unsigned long long tot = 0;
-  {
+  if (!queued) {
+    // pass 1: the top 12 bits of the key (or the sum of the S slices' histograms)
+    if (part && !peaked) {
+      const unsigned long long *src = part + (long)r * S * kNucBins;
+      for (int b = tid; b < kNucBins; b += kNucThreads) {
+        unsigned long long t = 0;
+        for (int sg = 0; sg < S; ++sg) t += src[(long)sg * kNucBins + b];
+        hist[b] = t;
+      }
+    } else {
+      nuc_visit(row, V, vec, [&](float v, int) {
+        const unsigned long long e = nuc_mass(v, inv_td, m, etab);
+        if (e) atomicAdd(&hist[order_key(v) >> 20], e);
+      });
+    }
+    __syncthreads();
     unsigned long long g = 0;
     for (int b = tid; b < kNucBins; b += kNucThreads) g += hist[b];
-    tot = block_excl_scan_u64(g, wtot);   // the last thread holds the total of the others
-    tot += g;
-    __syncthreads();
-    if (tid == kNucThreads - 1) sh_above = tot;
-    __syncthreads();
-    tot = sh_above;
+    tot = block_sum_u64(g, wtot);
+    if (tot == 0) {           // no mass (every logit -inf or NaN): keep every id
+      if (tid == 0) out[(long)r * out_stride] = NucRow{m, 0.0, 0u, 0x7fffffff};
+      return;
+    }
+    thr = top_p * (double)tot;
   }
-  if (tot == 0) {           // no mass (every logit -inf or NaN): keep every id
-    if (tid == 0) out[(long)r * out_stride] = NucRow{m, 0.0, 0u, 0x7fffffff};
-    return;
-  }
-  const double thr = top_p * (double)tot;
   nuc_find_bin(hist, kNucBins, 0ull, thr, wtot, &sh_bin, &sh_above);
   const uint32_t b1 = (uint32_t)sh_bin;
-  unsigned long long above = sh_above;
+  above = sh_above;
 
   // pass 2: the logits of bin b1 (a few percent of the row) gathered into LDS, so that
   // the masses of the finer bins are taken by full waves, and the last bits need no
   // further pass over the row; more than kNucQueue of them (heavy ties, narrow rows of
   // equal logits) take the two finer passes over the row instead
-  if (tid == 0) sh_qn = 0u;
+  __syncthreads();
+  if (!queued && tid == 0) sh_qn = 0u;
   for (int b = tid; b < kNucBins; b += kNucThreads) hist[b] = 0ull;
   __syncthreads();
-  nuc_visit(row, V, vec, [&](float v, int x) {
-    if ((order_key(v) >> 20) == b1) {
-      const unsigned slot = atomicAdd(&sh_qn, 1u);
-      if (slot < kNucQueue) {
-        qv[slot] = v;
-        qx[slot] = x;
-      }
-    }
-  });
-  __syncthreads();
-  const unsigned qn = sh_qn;
-  const bool queued = qn <= (unsigned)kNucQueue;
+  if (!queued) {
+    nuc_visit(row, V, vec, [&](float v, int x) {
+      if ((order_key(v) >> 20) == b1) push(v, x);
+    });
+    __syncthreads();
+    qn = sh_qn;
+    queued = qn <= (unsigned)kNucQueue;
+  }
   if (queued) {
     for (unsigned i = tid; i < qn; i += kNucThreads) {
       const float v = qv[i];
-      atomicAdd(&hist[(order_key(v) >> 8) & 0xfffu], nuc_mass(v, inv_td, m, etab));
+      const uint32_t k = order_key(v);
+      if ((k >> 20) == b1) atomicAdd(&hist[(k >> 8) & 0xfffu], nuc_mass(v, inv_td, m, etab));
     }
   } else {
     nuc_visit(row, V, vec, [&](float v, int) {
@@ -957,13 +1097,13 @@ void launch_nucleus(const char *name, int n_rows, int V, double inv_td, double t
                     unsigned long long *part, hipStream_t s) {
   if (n_rows <= 0) return;
   TraceScope ts(name, s);
-  // fewer than 128 rows leave CUs idle: their first pass is split over up to 8 workgroups per row
+  // fewer than 128 rows leave CUs idle: their first pass is split over up to kNucMaxSplit workgroups per row
   int S = part ? kNucSplitRows / n_rows : 1;
   if (S > kNucMaxSplit) S = kNucMaxSplit;
   if (S < 2 || V < S * 4096) S = 1;
   if (S > 1)
-    hipLaunchKernelGGL(nucleus_hist_kernel, dim3(n_rows * S), dim3(kNucThreads), 0, s, V, inv_td, logits, row_stride,
-                       st, nch, S, part);
+    hipLaunchKernelGGL(nucleus_hist_kernel, dim3(n_rows * S), dim3(kNucThreads), 0, s, V, inv_td, top_p, logits,
+                       row_stride, st, nch, S, part);
   hipLaunchKernelGGL(nucleus_kernel, dim3(n_rows), dim3(kNucThreads), 0, s, V, inv_td, top_p, logits, row_stride, st,
                      nch, S > 1 ? part : nullptr, S, out, out_stride);
 }

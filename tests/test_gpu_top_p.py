@@ -46,6 +46,22 @@ def _logits(shape, kind, *tags):
         z = np.round(z * 2.0) / 2.0
     elif kind == "flat":        # nearly every logit equal: the boundary inside a run of ~10^5 ties
         z = np.where(synth.stream(3, "flat", *tags).random(shape) < 1e-3, z * 3.0, 0.0)
+    elif kind in ("peaked", "plateau", "wide", "tail"):
+        g, V = synth.stream(3, "peak", *tags), shape[-1]
+        rows = z.reshape(-1, V)
+        for r in rows:
+            if kind == "peaked":      # a language model's row: sixteen likely ids over a broad floor
+                r[g.integers(0, V, 16)] = 14.0 - 1.2 * np.arange(16) + 0.5 * g.standard_normal(16)
+            elif kind == "plateau":   # 400 equal logits around the boundary, more than are ranked by counting
+                r[g.integers(0, V, 400)] = 8.0
+                r[g.integers(0, V)] = 13.5
+            elif kind == "wide":      # 20000 equal likely ids side by side, more than are queued
+                lo = int(g.integers(0, V - 20000))
+                r[:] = -20.0
+                r[lo:lo + 20000] = 0.0
+                r[g.integers(0, V)] = 6.1
+            else:                     # one likely id, the rest of the mass in ids too unlikely to queue
+                r[g.integers(0, V)] = np.log(0.1 * np.exp(r.astype(np.float64)).sum())
     return z.astype(np.float32)
 
 
@@ -61,6 +77,16 @@ def _logits(shape, kind, *tags):
     (1, 1, 151936, 1.0, 0.7, "normal"),        # one sequence: the first pass split over 8 workgroups
     # a head close to the target (zq = zt + 0.1 N(0, 1)): most drafts accepted, so the deep
     # prefixes and the bonus draw from the last target row's nucleus are compared
+    # peaked rows, queued in one pass: ranked by counting, by the radix selection over the queue, too
+    # many to queue, and the boundary past the queue; one block per row and split over blocks
+    (64, 3, 151936, 1.0, 0.7, "peaked"),
+    (5, 2, 32001, 0.7, 0.95, "peaked"),
+    (48, 2, 20000, 1.0, 0.7, "plateau"),
+    (6, 1, 151936, 1.0, 0.8, "plateau"),
+    (44, 2, 50257, 1.0, 0.95, "wide"),
+    (16, 0, 151936, 1.0, 0.95, "wide"),
+    (44, 2, 50256, 1.0, 0.7, "tail"),
+    (16, 0, 151936, 1.0, 0.7, "tail"),
     (64, 3, 151936, 1.0, 0.7, "overlap"),
     (32, 7, 151936, 1.0, 0.7, "overlap"),
 ])
