@@ -961,6 +961,7 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
       const unsigned long long *src = part + (long)r * S * kNucBins;
       for (int b = tid; b < kNucBins; b += kNucThreads) {
         unsigned long long t = 0;
+#pragma unroll 8
         for (int sg = 0; sg < S; ++sg) t += src[(long)sg * kNucBins + b];
         hist[b] = t;
       }
