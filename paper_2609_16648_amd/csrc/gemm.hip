@@ -514,8 +514,13 @@ void launch_f32(const GemmF &g, hipStream_t s) {
 // fragments from L2).  EPI_STATS: the softmax statistics of Y / T are taken per
 // row over the wave's own range (float32 terms, summed per lane in float32, the
 // 16 lane sums of a row in float64), one RowStat per (row, wave): the tiles of
-// the draw are the waves' ranges.
+// the draw are the waves' ranges.  Up to 16 and 32 rows have instances with one and
+// two row tiles: the products and the fragment reads for padding rows were not hidden
+// by the weight stream (7 rows: 126 us per launch with four row tiles, 117 with one).
 constexpr int kLmStrips = 10;
+// Outputs from this width (two columns of 128 per CU) are wide enough to give every wave strips
+// of its own; narrower ones are split along K by the tiled kernel.
+constexpr int kLmStripsMinN = 256 * 128;
 // Two slots: one k-step (10 KiB of weights per wave) in flight while the other is consumed.
 // With four waves per CU that is about as much as the HBM queues serve best; deeper rings put
 // more in flight and were slower (measured at 64 rows: 2 slots 146 us per launch, 4 slots
@@ -538,7 +543,8 @@ struct GemmL {
   float inv_t;
 };
 
-template <int EPI>
+// AT: 16-row tiles of activations (1, 2 or 4)
+template <int EPI, int AT>
 __global__ __launch_bounds__(256) void lm_strips_kernel(GemmL g) {
   const int lane = threadIdx.x & 63, j = lane & 15, g4 = lane >> 4;
   const int wv = threadIdx.x >> 6;
@@ -554,23 +560,26 @@ __global__ __launch_bounds__(256) void lm_strips_kernel(GemmL g) {
 #pragma unroll
   for (int t = 0; t < kLmStrips; ++t) wb[t] = g.W + w_tile(s0 + min(t, n - 1), 0, ksteps) + lane * 8;
 
-  floatx4_t acc[4][kLmStrips];
+  floatx4_t acc[AT][kLmStrips];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < AT; ++a)
 #pragma unroll
     for (int t = 0; t < kLmStrips; ++t) acc[a][t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
-  // Activation chunk c in As[c % 2], 1 KiB per (k-step st, row tile a) at (4 st + a) KiB:
+  // Activation chunk c in As[c % 2], 1 KiB per (k-step st, row tile a) at (AT st + a) KiB:
   // lane l holds row 16 a + (l & 15) (rows past M re-read row M - 1), k 8 (l >> 4) ..
   // of that step, i.e. the A operand as the MFMA takes it.  Wave w stages the loads
-  // u = kLmChunk w .. kLmChunk (w + 1) - 1.
-  __shared__ uint16_t As[2][kLmChunk * 4 * 512];
+  // u = AT w .. AT (w + 1) - 1.  (The array is larger than that needs with few row tiles, so
+  // that a CU holds one workgroup whatever its registers: ranges are cut for one wave per SIMD.)
+  constexpr int kAsElems = kLmChunk * AT * 512;
+  static_assert(kLmChunk == 4, "four waves stage AT loads each");
+  __shared__ uint16_t As[2][kAsElems > 22 * 1024 ? kAsElems : 22 * 1024];
   auto issue_a = [&](int c) {
     const int cc = min(c, nchunks - 1);   // past the end: the last chunk again, into the free buffer
     uint16_t *dst = &As[c % 2][0];
 #pragma unroll
-    for (int q = 0; q < kLmChunk; ++q) {
-      const int u = wv * kLmChunk + q, st = u >> 2, a = u & 3;
+    for (int q = 0; q < AT; ++q) {
+      const int u = wv * AT + q, st = u / AT, a = u % AT;
       const uint16_t *src = g.X + (long)min(16 * a + j, g.M - 1) * g.ldx + (kLmChunk * cc + st) * 32 + 8 * g4;
       __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)(dst + u * 512), 16, 0, 0);
     }
@@ -603,12 +612,12 @@ __global__ __launch_bounds__(256) void lm_strips_kernel(GemmL g) {
         if (d == 0) issue_a(c + 1);   // into the buffer of chunk c - 1, released by the last barrier
         load_w_step((d + kLmRing - 1) % kLmRing, min(s + kLmRing - 1, ksteps - 1));
         __builtin_amdgcn_sched_barrier(0);
-        bf16x8_t af[4];
+        bf16x8_t af[AT];
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-          af[a] = as_bf16x8(*reinterpret_cast<const uint4 *>(&As[c % 2][(d * 4 + a) * 512 + lane * 8]));
+        for (int a = 0; a < AT; ++a)
+          af[a] = as_bf16x8(*reinterpret_cast<const uint4 *>(&As[c % 2][(d * AT + a) * 512 + lane * 8]));
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < AT; ++a)
 #pragma unroll
           for (int t = 0; t < NS; ++t)
             acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], as_bf16x8(rw[d % kLmRing][t]), acc[a][t], 0, 0, 0);
@@ -627,7 +636,7 @@ __global__ __launch_bounds__(256) void lm_strips_kernel(GemmL g) {
 
   // lane holds C[row 16 a + 4 g4 + r][col 16 (s0 + t) + j]
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
+  for (int a = 0; a < AT; ++a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = 16 * a + 4 * g4 + r;
@@ -653,7 +662,7 @@ __global__ __launch_bounds__(256) void lm_strips_kernel(GemmL g) {
     float *pf = sh_part[wv], *rmax = sh_rmax[wv];
     int *pa = sh_arg[wv];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
+    for (int a = 0; a < AT; ++a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float vmax = -INFINITY;
@@ -680,7 +689,7 @@ __global__ __launch_bounds__(256) void lm_strips_kernel(GemmL g) {
     rmax[lane] = M;
     wave_lds_sync();
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
+    for (int a = 0; a < AT; ++a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = 16 * a + 4 * g4 + r;
@@ -714,7 +723,7 @@ int lm_resident_waves() {
   int v = cache[dev].load();
   if (v > 0) return v;
   int per_cu = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lm_strips_kernel<EPI_STATS>, 256, 0) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lm_strips_kernel<EPI_STATS, 4>, 256, 0) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu < 1 || cus < 1) {
     (void)hipGetLastError();
     return 1024;
@@ -722,6 +731,14 @@ int lm_resident_waves() {
   v = per_cu * cus * 4;
   cache[dev].store(v);
   return v;
+}
+
+template <int EPI>
+void launch_strips(const GemmL &l, hipStream_t s) {
+  const dim3 grid((l.geo.tiles + 3) / 4), block(256);
+  if (l.M <= 16) hipLaunchKernelGGL((lm_strips_kernel<EPI, 1>), grid, block, 0, s, l);
+  else if (l.M <= 32) hipLaunchKernelGGL((lm_strips_kernel<EPI, 2>), grid, block, 0, s, l);
+  else hipLaunchKernelGGL((lm_strips_kernel<EPI, 4>), grid, block, 0, s, l);
 }
 
 template <int MT, int NT, int WM, int EPI, int CW>
@@ -856,13 +873,17 @@ TileGeom plan_lm_head(int dtype, int M, int V, int K, bool *strips_kernel) {
 int launch_gemm(const char *name, int dtype, int epi, int M, int N, int K, const void *X, int ldx, const void *W,
                 void *Y, long ldy, float *part, hipStream_t s, RowStat *tile_stats, float inv_t, bool defer_reduce) {
   if (M <= 0) return 1;
-  if (dtype == GM_BF16 && epi == EPI_STATS) {
+  // The LM head at M <= 64, with statistics or without, takes the strip ranges: a verify layer with
+  // LM head at 4 / 16 / 32 / 64 rows 198.6 / 205 / 214 / 227 us against 198.9 / 214 / 232 / 257 with the
+  // tiled kernel (V 151936, K 2560), 283 / 292 / 299 / 317 against 291 / 308 / 327 / 363 (V 151680, K 4096).
+  if (dtype == GM_BF16 && (epi == EPI_STATS || (epi == EPI_STORE_F32 && N >= kLmStripsMinN))) {
     bool strips = false;
     const TileGeom geo = plan_lm_head(dtype, M, N, K, &strips);
     if (strips) {
       GemmL l{(const uint16_t *)X, (const uint16_t *)W, (float *)Y, ldy, M, K, ldx, geo, tile_stats, inv_t};
       TraceScope ts(name, s);
-      hipLaunchKernelGGL(lm_strips_kernel<EPI_STATS>, dim3((geo.tiles + 3) / 4), dim3(256), 0, s, l);
+      if (epi == EPI_STATS) launch_strips<EPI_STATS>(l, s);
+      else launch_strips<EPI_STORE_F32>(l, s);
       return 1;
     }
   }

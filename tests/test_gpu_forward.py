@@ -353,3 +353,32 @@ def test_strip_ranges_with_idle_waves():
     print("[strip ranges, 10248 strips] logits rel err vs contract %.3e" % err, flush=True)
     assert err < 1e-2
     _check_stats("strip ranges, 10248 strips", stats, logits, 1.0)
+
+
+@pytest.mark.parametrize("B,k", [(1, 0), (16, 0), (17, 0), (8, 3), (11, 2), (16, 3), (13, 4)])
+def test_lm_head_rows_by_kernel(B, k):
+    # 1, 16, 17, 32, 33, 64 and 65 rows: the edges of the strip-range kernel's row tiles and of its
+    # range, on a vocabulary that leaves the last waves short ranges; the statistics of the same rows
+    # agree with the logits
+    need_gpu()
+    shape = dataclasses.replace(synth.QWEN3_4B_LAYER, hidden=256, n_heads=4, n_kv_heads=2, ffn=512, vocab=128 * 263)
+    W = synth.model_weights(shape)
+    lens = 5 + 3 * np.arange(B)
+    caches = synth_caches(shape, lens, 1)
+    tokens = synth.token_ids(B * (k + 1), shape.vocab, 1, "lm-rows").reshape(B, k + 1)
+    model = gm.DeviceModel(shape, W)
+    logits, _ = _gpu_forward(model, device_cache(shape, caches, lens, k + 1), tokens)
+    ref, _, _ = oracle.verify_forward(shape, W, caches, tokens, lens, CONTRACT)
+    assert rel_err(logits, ref) < 1e-2
+    st = gm.new_row_stats(B, k + 1)
+    lg = torch.empty((B, k + 1, shape.vocab), dtype=torch.float32, device="cuda")
+    hid = torch.empty((B, k + 1, shape.hidden), dtype=torch.float32, device="cuda")
+    gm.verify_forward(model, device_cache(shape, caches, lens, k + 1), i32(tokens), lg, hid, gm.Workspace(),
+                      target_stats=st)
+    torch.cuda.synchronize()
+    mx, am, sm = gm.decode_row_stats(st)
+    z = lg.cpu().numpy()
+    np.testing.assert_array_equal(mx, z.max(-1))
+    np.testing.assert_array_equal(am, z.argmax(-1))
+    # float32 exponentials (2 ulp), summed in float32 over at most ten ids, then in float64
+    np.testing.assert_allclose(sm, np.exp(z.astype(np.float64) - mx[..., None]).sum(-1), rtol=1e-6)
