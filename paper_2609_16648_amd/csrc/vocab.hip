@@ -588,8 +588,11 @@ void launch_record_topk(int B, int k, int V, float inv_t, int topk, const float 
 //  Peaked rows, the common case of a language model, need one pass and no histogram
 // atomics over the row: a pass sums every id's mass in registers and queues the few
 // ids likely enough to reach the boundary; if the queue's mass reaches top_p of the
-// row's, the boundary is among them.  Otherwise, and for flat rows, the passes above
-// run.  Both find the same boundary from the same integers.
+// row's, the boundary is among them.  The same pass bins the ids that could hold the
+// boundary at all (the rest has less than 1 - top_p) by their exponent, so a boundary
+// behind the queue costs one more pass, which gathers its band.  Flat rows, and bands
+// too large for LDS, take the passes above.  All find the same boundary from the same
+// integers.
 constexpr int kNucThreads = 1024;
 constexpr int kNucBins = 4096;
 constexpr int kNucQueue = 12288;     // logits and ids of the boundary's 12-bit bin kept in LDS (96 KiB)
@@ -601,7 +604,8 @@ constexpr int kNucTieRank = 2048;    // ties at the boundary ranked in LDS (more
 constexpr double kNucFlat = 64.0;
 constexpr double kNucTail = 2048.0;
 constexpr int kNucRank = 256;        // queued ids ranked by counting (more: the radix selection over the queue)
-constexpr int kNucSliceMax = kNucBins - 2;   // ids queued by one slice of a split pass
+constexpr int kNucBands = 512;       // bands of the exponent, 1/16 wide, the largest last
+constexpr int kNucSliceMax = kNucBins - kNucBands - 2;   // ids queued by one slice of a split pass
 
 // exp(y) 2^44 for -32 <= y <= 0 by Tang's table-driven reduction (ACM TOMS 15(2), 1989):
 // y = (kNucTab q + j) ln2 / kNucTab + r with |r| <= ln2 / (2 kNucTab) = 1.7e-4, exp(y) = 2^q
@@ -630,11 +634,15 @@ __device__ __forceinline__ void nuc_exp_table(double *tab) {
   for (int j = threadIdx.x; j < kNucTab; j += blockDim.x) tab[j] = exp2(44.0 + (double)j / kNucTab);
 }
 
-// mass of one id in 2^-44 units (the same operations at every call: no contraction); y gets
-// its exponent z / T - m
-__device__ __forceinline__ unsigned long long nuc_mass(float v, double inv_td, double m, const double *tab, double &y) {
+// exponent z / T - m of one id (the same operations at every call: no contraction)
+__device__ __forceinline__ void nuc_exponent(float v, double inv_td, double m, double &y) {
 #pragma clang fp contract(off)
   y = (double)v * inv_td - m;
+}
+
+// mass of one id in 2^-44 units; y gets its exponent
+__device__ __forceinline__ unsigned long long nuc_mass(float v, double inv_td, double m, const double *tab, double &y) {
+  nuc_exponent(v, inv_td, m, y);
   if (!(y >= -32.0)) return 0ull;          // exp(-32) 2^44 < 0.5: rounds to 0 (and -inf, NaN)
   // exp(y) 2^44 < 2^52: adding 2^52 leaves its nearest integer (ties to even) in the
   // low mantissa bits
@@ -790,6 +798,21 @@ __device__ __forceinline__ double nuc_cut(double S, double top_p) {
   return c > -32.0 ? c : -32.0;
 }
 
+// Ids below this exponent hold less than 1 - top_p of the row's mass together.  Up to
+// kNucBandTopP no bands are kept (for 256 rows they take 10 us, 50 without): there the queue
+// misses the boundary only in rows that put 1 - kNucBandTopP or more of their mass in over
+// kNucTail unlikely ids, and those take the histogram passes.
+constexpr double kNucBandTopP = 0.8;
+__device__ __forceinline__ double nuc_guard(double S, double top_p, int V) {
+  if (top_p <= kNucBandTopP) return INFINITY;
+  const double c = log(S * (1.0 - top_p) / V);
+  return c > -32.0 ? c : -32.0;
+}
+__device__ __forceinline__ int nuc_band(double y) {   // y >= -32; grows with y
+  const int b = (int)(-y * 16.0);
+  return kNucBands - 1 - (b < 0 ? 0 : b < kNucBands ? b : kNucBands - 1);
+}
+
 // sum of one value per thread over the block; wtot >= 16 entries.  Holds barriers.
 __device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v, unsigned long long *wtot) {
 #pragma unroll
@@ -806,8 +829,8 @@ __device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v
 // few rows to fill the chip: workgroup (r, s) takes its slice of row r (ids [lo, hi),
 // lo and hi multiples of 4) to part[(r S + s) kNucBins ...].  Flat rows: the slice's
 // histogram; the selection sums the S of them (exact integers: the same result as one
-// pass).  Peaked rows: the slice's mass, the number of its ids past the cut, and those
-// ids (logit bits in the upper half), up to kNucSliceMax of them.
+// pass).  Peaked rows: the slice's mass, the number of its ids past the cut, the masses of
+// its bands, and those ids (logit bits in the upper half), up to kNucSliceMax of them.
 __global__ __launch_bounds__(kNucThreads) void nucleus_hist_kernel(int V, double inv_td, double top_p,
                                                                    const float *__restrict__ logits, long row_stride,
                                                                    const RowStat *__restrict__ st, int nch, int S,
@@ -830,18 +853,21 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_hist_kernel(int V, double
   const bool vec = (V & 3) == 0 && (row_stride & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
   unsigned long long *dst = part + ((long)r * S + sg) * kNucBins;
   if (nuc_peaked(mass)) {
-    const double cut = nuc_cut(mass, top_p);
+    const double cut = nuc_cut(mass, top_p), guard = nuc_guard(mass, top_p, V);
     unsigned long long t = 0;
     nuc_visit(row + lo, hi - lo, vec, [&](float v, int x) {
       double y;
-      t += nuc_mass(v, inv_td, m, etab, y);
+      const unsigned long long e = nuc_mass(v, inv_td, m, etab, y);
+      t += e;
+      if (y >= guard) atomicAdd(&hist[nuc_band(y)], e);
       if (y >= cut) {
         const unsigned slot = atomicAdd(&sh_qn, 1u);
         if (slot < (unsigned)kNucSliceMax)
-          dst[2 + slot] = ((unsigned long long)__float_as_uint(v) << 32) | (unsigned)(lo + x);
+          dst[2 + kNucBands + slot] = ((unsigned long long)__float_as_uint(v) << 32) | (unsigned)(lo + x);
       }
     });
     t = block_sum_u64(t, wtot);
+    for (int b = tid; b < kNucBands; b += kNucThreads) dst[2 + b] = hist[b];
     if (tid == 0) {
       dst[0] = t;
       dst[1] = sh_qn;
@@ -905,15 +931,23 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
           if (n > kNucSliceMax) atomicAdd(&sh_qn, (unsigned)kNucQueue + 1u);   // ids are missing: not queued
         }
         for (unsigned i = tid; i < (unsigned)n && i < (unsigned)kNucSliceMax; i += kNucThreads) {
-          const unsigned long long c = src[(long)sg * kNucBins + 2 + i];
+          const unsigned long long c = src[(long)sg * kNucBins + 2 + kNucBands + i];
           push(__uint_as_float((uint32_t)(c >> 32)), (int)(uint32_t)c);
         }
       }
+      for (int b = tid; b < kNucBands; b += kNucThreads) {
+        unsigned long long h = 0;
+#pragma unroll 8
+        for (int sg = 0; sg < S; ++sg) h += src[(long)sg * kNucBins + 2 + b];
+        hist[b] = h;
+      }
     } else {
-      const double cut = nuc_cut(S_row, top_p);
+      const double cut = nuc_cut(S_row, top_p), guard = nuc_guard(S_row, top_p, V);
       nuc_visit(row, V, vec, [&](float v, int x) {
         double y;
-        t += nuc_mass(v, inv_td, m, etab, y);
+        const unsigned long long e = nuc_mass(v, inv_td, m, etab, y);
+        t += e;
+        if (y >= guard) atomicAdd(&hist[nuc_band(y)], e);
         if (y >= cut) push(v, x);
       });
     }
@@ -948,6 +982,30 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
       }
       return;
     }
+    if (!queued && tot > 0) {
+      // the boundary's band, then its ids from the row
+      unsigned long long h = 0;
+      for (int b = tid; b < kNucBands; b += kNucThreads) h += hist[b];
+      h = block_sum_u64(h, wtot);
+      if ((double)h >= thr) {
+        nuc_find_bin(hist, kNucBands, 0ull, thr, wtot, &sh_bin, &sh_above);
+        const int band = sh_bin;
+        above = sh_above;
+        if (tid == 0) sh_qn = 0u;
+        __syncthreads();
+        nuc_visit(row, V, vec, [&](float v, int x) {
+          double y;
+          nuc_exponent(v, inv_td, m, y);
+          if (y >= -32.0 && nuc_band(y) == band) push(v, x);
+        });
+        __syncthreads();
+        qn = sh_qn;
+        queued = qn <= (unsigned)kNucQueue;
+        if (!queued) above = 0;
+      }
+    }
+    __syncthreads();
+    for (int b = tid; b < kNucBands; b += kNucThreads) hist[b] = 0ull;   // (the other bins are still 0)
     __syncthreads();
     if (queued) {
       for (unsigned i = tid; i < qn; i += kNucThreads)
@@ -981,7 +1039,7 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
     }
     thr = top_p * (double)tot;
   }
-  nuc_find_bin(hist, kNucBins, 0ull, thr, wtot, &sh_bin, &sh_above);
+  nuc_find_bin(hist, kNucBins, above, thr, wtot, &sh_bin, &sh_above);
   const uint32_t b1 = (uint32_t)sh_bin;
   above = sh_above;
 
