@@ -53,6 +53,16 @@ def test_record_matches_oracle(B, k, V, topk, T):
           flush=True)
 
 
+@pytest.mark.parametrize("B,k,V,topk", [(3, 1, 65536, 64), (3, 1, 65537, 1), (2, 2, 200000, 64)])
+def test_record_run_bounds(B, k, V, topk):
+    # 256 runs (ranked directly), 320 runs with most of the last chunk empty (first bound over sets of
+    # runs), and 13 chunks of statistics (more than are combined at once)
+    need_gpu()
+    zt = synth.normal_logits((B, k + 1, V), 3, "rec-runs", B, k, V)
+    ids, logp, _, _ = _gpu_record(zt, np.zeros((B, k), dtype=np.int64), topk, 1.0)
+    _check(zt, k, 1.0, topk, ids, logp)
+
+
 def test_record_ties_and_flat_rows():
     # row 0: 300 ids share the maximum, the record takes the 64 lowest of them; row 1: a flat
     # row (every id ties, the bisection path), ids 0..63 at log(1/V)
