@@ -196,14 +196,14 @@ void run_mtp_draft(const gm_model_config &cfg, const gm_mtp_weights &mtp, const 
     launch_gemm("mtp_gemm_lm_head", dt, EPI_STATS, B, V, H, nbuf, H, shared.lm_head, zl, (long)k * V, part, s, tiles,
                 inv_t);
     const TileGeom geo = plan_lm_head(dt, B, V, H);
-    if (top_p < 1.0) {   // top-p: a draw from each row's nucleus (a selection, then an inverse-CDF scan)
+    if (top_p < 1.0) {   // top-p: a draw from each row's nucleus, by the selection or an inverse-CDF scan
       // the nuclei go to the caller's draft_nucleus[:, j] when given (the accept's handoff)
       NucRow *nuc = draft_nucleus ? draft_nucleus + j : (NucRow *)(ws + p.nuc);
       const int ns = draft_nucleus ? k : 1;
       RowSel *sel = (RowSel *)(ws + p.sel);
+      const NucDraw draw{u_draft + j, k, drafts + j, k, sel, inv_t};
       launch_nucleus("draft_nucleus", B, V, inv_td, top_p, zl, (long)k * V, tiles, geo.tiles, nuc, ns,
-                     (unsigned long long *)(ws + p.nucpart), s);
-      launch_nucleus_select(B, zl, (long)k * V, nuc, ns, u_draft + j, k, drafts + j, k, sel, s);
+                     (unsigned long long *)(ws + p.nucpart), s, &draw);
       launch_residual_draw("draft_nucleus_chunk", "draft_nucleus_scan", B, V, inv_t, sel, (double *)(ws + p.wsum),
                            (double *)(ws + p.psum), true, s);
     } else {

@@ -126,13 +126,19 @@ void launch_accept_decide(int B, int k, int V, int mode, float inv_t, double inv
 constexpr int kNucSplitRows = 256;     // rows x workgroups per row of a split first pass
 constexpr int kNucMaxSplit = 16;
 constexpr size_t kNucPartBytes = (size_t)kNucSplitRows * 4096 * 8;
+// draw (may be null): also a draw from row r's nucleus with u[r * u_stride], made into dst[r * dst_stride]
+// where the nucleus was found among few ids (sel[r].active = 0), else left in sel[r] for launch_residual_draw
+struct NucDraw {
+  const float *u;
+  int u_stride;
+  int32_t *dst;
+  int dst_stride;
+  RowSel *sel;          // null: no draw
+  float inv_t;
+};
 void launch_nucleus(const char *name, int n_rows, int V, double inv_td, double top_p, const float *logits,
                     long row_stride, const RowStat *st, int nch, NucRow *out, int out_stride,
-                    unsigned long long *part, hipStream_t s);
-// sel[b] := a draw from the nucleus nuc[b * nuc_stride] of row b (logits + b * row_stride)
-// with the uniform u[b * u_stride], into dst[b * dst_stride]
-void launch_nucleus_select(int B, const float *logits, long row_stride, const NucRow *nuc, int nuc_stride,
-                           const float *u, int u_stride, int32_t *dst, int dst_stride, RowSel *sel, hipStream_t s);
+                    unsigned long long *part, hipStream_t s, const NucDraw *draw = nullptr);
 // nucleus false: every row of sel keeps every id (top-p 1), and the kernels skip the nucleus tests
 void launch_residual_draw(const char *chunk_name, const char *scan_name, int B, int V, float inv_t, const RowSel *sel,
                           double *wsum, double *psum, bool nucleus, hipStream_t s);

@@ -932,11 +932,34 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_hist_kernel(int V, double
   for (int b = tid; b < kNucBins; b += kNucThreads) dst[b] = hist[b];
 }
 
+// row r's nucleus (by one thread), and the row's draw for the scan over the vocabulary
+__device__ __forceinline__ void nuc_write(const NucRow &n, int r, NucRow *out, int out_stride, const NucDraw &draw,
+                                          const float *row) {
+  out[(long)r * out_stride] = n;
+  if (!draw.sel) return;
+  RowSel rs;
+  rs.p_row = row;
+  rs.q_row = nullptr;
+  rs.mp = n.m;
+  rs.sp = n.s;
+  rs.mq = 0.0;
+  rs.sq = 1.0;
+  rs.u = (double)draw.u[(long)r * draw.u_stride];
+  rs.dst = draw.dst + (long)r * draw.dst_stride;
+  rs.active = 1;
+  rs.pad = 0;
+  rs.pkey = n.key;
+  rs.pid = n.idt;
+  rs.qkey = 0;
+  rs.qid = 0x7fffffff;
+  draw.sel[r] = rs;
+}
+
 __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_td, double top_p,
                                                               const float *__restrict__ logits, long row_stride,
                                                               const RowStat *__restrict__ st, int nch,
                                                               const unsigned long long *__restrict__ part, int S,
-                                                              NucRow *__restrict__ out, int out_stride) {
+                                                              NucRow *__restrict__ out, int out_stride, NucDraw draw) {
   __shared__ unsigned long long hist[kNucBins];
   __shared__ float qv[kNucQueue];
   __shared__ int qx[kNucQueue];
@@ -1012,10 +1035,16 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
     }
     if (queued && qn <= (unsigned)kNucRank) {
       // few: each id's running mass is the mass of the ids ranked before it; the boundary is the
-      // id whose own mass takes it to thr, and the ids of equal logit past it are left out
+      // id whose own mass takes it to thr, and the ids of equal logit past it are left out.  The
+      // ids before thr are the whole nucleus, so a draw from it is made here: their weights (the
+      // terms the scan over the vocabulary would take) in id order, summed by one thread.
       unsigned long long *qm = hist;
       for (unsigned i = tid; i < qn; i += kNucThreads) qm[i] = nuc_mass(qv[i], inv_td, m, etab);
+      if (tid == 0) sh_bin = 0;
       __syncthreads();
+      double *const qw = etab, *const sw = etab + kNucRank;   // (the table is done with)
+      int *const sx = reinterpret_cast<int *>(etab + 2 * kNucRank);
+      double w_own = 0.0;   // qn <= kNucRank <= kNucThreads: one id per thread
       for (unsigned i = tid; i < qn; i += kNucThreads) {
         const uint32_t k = order_key(qv[i]);
         const int x = qx[i];
@@ -1029,6 +1058,34 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
         }
         if ((double)before < thr && (double)(before + qm[i]) >= thr)
           out[(long)r * out_stride] = NucRow{m, (double)(before + qm[i]) * 0x1p-44, k, more ? x : 0x7fffffff};
+        w_own = (double)before < thr ? (double)expf(qv[i] * draw.inv_t - (float)m) : -1.0;   // -1: not kept
+        qw[i] = w_own;
+      }
+      if (!draw.sel) return;
+      __syncthreads();
+      if (tid < (int)qn && w_own >= 0.0) {
+        int at = 0;
+        for (unsigned j = 0; j < qn; ++j) at += qw[j] >= 0.0 && qx[j] < qx[tid];
+        sw[at] = w_own;
+        sx[at] = qx[tid];
+        atomicAdd(&sh_bin, 1);
+      }
+      __syncthreads();
+      if (tid == 0) {
+        const int n = sh_bin;
+        double Z = 0.0, run = 0.0;
+#pragma unroll 8
+        for (int c = 0; c < n; ++c) Z += sw[c];
+        const double t = (double)draw.u[(long)r * draw.u_stride] * Z;
+        int hit = -1, last = sx[n - 1];
+#pragma unroll 8
+        for (int c = 0; c < n; ++c) {
+          run += sw[c];
+          if (hit < 0 && run > t) hit = sx[c];
+          if (sw[c] > 0.0) last = sx[c];
+        }
+        draw.dst[(long)r * draw.dst_stride] = hit >= 0 ? hit : last;
+        draw.sel[r].active = 0;
       }
       return;
     }
@@ -1084,7 +1141,7 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
     for (int b = tid; b < kNucBins; b += kNucThreads) g += hist[b];
     tot = block_sum_u64(g, wtot);
     if (tot == 0) {           // no mass (every logit -inf or NaN): keep every id
-      if (tid == 0) out[(long)r * out_stride] = NucRow{m, 0.0, 0u, 0x7fffffff};
+      if (tid == 0) nuc_write(NucRow{m, 0.0, 0u, 0x7fffffff}, r, out, out_stride, draw, row);
       return;
     }
     thr = top_p * (double)tot;
@@ -1198,12 +1255,13 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
     __syncthreads();
     idt = sh_idt;
   }
-  if (tid == 0) out[(long)r * out_stride] = NucRow{m, (double)(above + (unsigned long long)j * et) * 0x1p-44, key, idt};
+  if (tid == 0)
+    nuc_write(NucRow{m, (double)(above + (unsigned long long)j * et) * 0x1p-44, key, idt}, r, out, out_stride, draw, row);
 }
 
 void launch_nucleus(const char *name, int n_rows, int V, double inv_td, double top_p, const float *logits,
                     long row_stride, const RowStat *st, int nch, NucRow *out, int out_stride,
-                    unsigned long long *part, hipStream_t s) {
+                    unsigned long long *part, hipStream_t s, const NucDraw *draw) {
   if (n_rows <= 0) return;
   TraceScope ts(name, s);
   // fewer than 128 rows leave CUs idle: their first pass is split over up to kNucMaxSplit workgroups per row
@@ -1214,39 +1272,7 @@ void launch_nucleus(const char *name, int n_rows, int V, double inv_td, double t
     hipLaunchKernelGGL(nucleus_hist_kernel, dim3(n_rows * S), dim3(kNucThreads), 0, s, V, inv_td, top_p, logits,
                        row_stride, st, nch, S, part);
   hipLaunchKernelGGL(nucleus_kernel, dim3(n_rows), dim3(kNucThreads), 0, s, V, inv_td, top_p, logits, row_stride, st,
-                     nch, S > 1 ? part : nullptr, S, out, out_stride);
-}
-
-__global__ void nucleus_select_kernel(int B, const float *__restrict__ logits, long row_stride,
-                                      const NucRow *__restrict__ nuc, int nuc_stride, const float *__restrict__ u,
-                                      int u_stride,
-                                      int32_t *dst, int dst_stride, RowSel *__restrict__ sel) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const NucRow n = nuc[(long)b * nuc_stride];
-  RowSel rs;
-  rs.p_row = logits + (long)b * row_stride;
-  rs.q_row = nullptr;
-  rs.mp = n.m;
-  rs.sp = n.s;
-  rs.mq = 0.0;
-  rs.sq = 1.0;
-  rs.u = (double)u[(long)b * u_stride];
-  rs.dst = dst + (long)b * dst_stride;
-  rs.active = 1;
-  rs.pad = 0;
-  rs.pkey = n.key;
-  rs.pid = n.idt;
-  rs.qkey = 0;
-  rs.qid = 0x7fffffff;
-  sel[b] = rs;
-}
-
-void launch_nucleus_select(int B, const float *logits, long row_stride, const NucRow *nuc, int nuc_stride,
-                           const float *u, int u_stride, int32_t *dst, int dst_stride, RowSel *sel, hipStream_t s) {
-  if (B <= 0) return;
-  hipLaunchKernelGGL(nucleus_select_kernel, dim3((B + 63) / 64), dim3(64), 0, s, B, logits, row_stride, nuc,
-                     nuc_stride, u, u_stride, dst, dst_stride, sel);
+                     nch, S > 1 ? part : nullptr, S, out, out_stride, draw ? *draw : NucDraw{});
 }
 
 // ------------------------------------------------------------------ 3. inverse-CDF draw

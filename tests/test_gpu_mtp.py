@@ -267,3 +267,43 @@ def test_qwen_layer_bf16_mtp_top_p_draw_from_own_logits(qwen_mtp, B, temperature
     print("[mtp bf16 top-p %.1f B=%d T=%.1f] %d draws, %d identical to the oracle's, %d flagged"
           % (top_p, B, temperature, B * k, exact, flagged), flush=True)
     assert exact >= B * k - flagged - 2
+
+
+@pytest.mark.parametrize("B,temperature,top_p,scale", [(5, 1.0, 0.7, 6.0), (64, 1.0, 0.95, 4.0), (130, 0.7, 0.5, 5.0)])
+def test_qwen_layer_bf16_mtp_top_p_draw_peaked(qwen_mtp, B, temperature, top_p, scale):
+    # a confident head (the final norm scaled, so that the likeliest id holds percents of the mass and
+    # the nucleus tens to thousands of ids): drawn among the queued ids where the boundary is found there,
+    # by the scan over the vocabulary elsewhere, each against the oracle's draw from the same logits
+    need_gpu()
+    shape, W, Wm = qwen_mtp
+    Wm = dict(Wm, final_norm=Wm["final_norm"] * np.float32(scale))
+    k = 2
+    lens, caches, hidden, n, out, u = _inputs(shape, B, k, 1, 60, 9)
+    model, mtp = gm.DeviceModel(shape, W), gm.DeviceMtp(shape, Wm)
+    cache = device_cache(shape, caches, lens, 2 * k + 2)
+    drafts = torch.zeros((B, k), dtype=torch.int32, device="cuda")
+    dlog = torch.zeros((B, k, shape.vocab), dtype=torch.float32, device="cuda")
+    nuc = gm.new_nuclei(B, k)
+    gm.mtp_draft(model, mtp, cache, k, gm.GM_SAMPLE, t32(hidden), i32(n), i32(out), t32(u), drafts, dlog,
+                 gm.Workspace(), temperature=temperature, top_p=top_p, draft_nucleus=nuc)
+    torch.cuda.synchronize()
+    z, got = dlog.cpu().numpy(), drafts.cpu().numpy()
+    last = nuc[..., 20:24].contiguous().view(torch.int32)[..., 0].cpu().numpy()
+    assert (last > 0).all()
+    exact, flagged, sizes = 0, 0, []
+    for b in range(min(B, 40)):
+        for j in range(k):
+            pn, dist = oracle.nucleus(z[b, j], oracle.softmax(z[b, j].astype(np.float64) / temperature), top_p)
+            sizes.append(int((pn > 0).sum()))
+            if dist < 5e-9:
+                flagged += 1
+                continue
+            x, c, t = int(got[b, j]), np.cumsum(pn), float(u[b, j])
+            assert pn[x] > 0, (b, j, x)
+            # few ids share the mass, so the float32 terms (2 ulp and the rounding of z t - m, up to
+            # 2^-24 * 50) do not average out: 4e-6 of the mass, doubled for the normaliser
+            assert (c[x - 1] if x else 0.0) - 8e-6 <= t < c[x] + 8e-6, (b, j, x)
+            exact += int(oracle.inverse_cdf(pn, u[b, j])[0] == x)
+    print("[mtp peaked top-p %.2f B=%d] nuclei of %d..%d ids, %d draws identical, %d flagged"
+          % (top_p, B, min(sizes), max(sizes), exact, flagged), flush=True)
+    assert exact >= len(sizes) - flagged - 2
