@@ -27,12 +27,15 @@ size_t part_bytes(const gm_model_config &c, int M, bool with_proj) {
 }
 
 // GEMM into the float32 residual rows Y [M][N] followed by the RMSNorm of those
-// rows into nbuf: with a K split the reduce and the norm run as one kernel.
-void gemm_norm(const char *name, int dt, int epi, int M, int N, int K, const void *X, int ldx, const void *W,
-               float *Y, float *part, const void *norm_w, float eps, void *nbuf, hipStream_t s) {
+// rows into nbuf: with a K split the reduce and the norm run as one kernel.  In the
+// float32 path the norm is left to the GEMM that reads nbuf (the returned PendingNorm).
+PendingNorm gemm_norm(const char *name, int dt, int epi, int M, int N, int K, const void *X, int ldx, const void *W,
+                      float *Y, float *part, const void *norm_w, float eps, void *nbuf, hipStream_t s) {
   const int sp = launch_gemm(name, dt, epi, M, N, K, X, ldx, W, Y, N, part, s, nullptr, 1.f, true);
+  if (dt != GM_BF16) return PendingNorm{Y, norm_w, eps};
   if (sp > 1) launch_reduce_norm(dt, epi, M, N, sp, part, Y, norm_w, eps, nbuf, s);
   else launch_rmsnorm(dt, M, N, eps, Y, norm_w, nbuf, s);
+  return PendingNorm{};
 }
 
 // qkv projection: `splits` > 1 leaves the partials in `part` for the RoPE kernel to sum
@@ -104,10 +107,11 @@ void run_verify_forward(const gm_model_config &cfg, const gm_model_weights &w, c
   // the RMSNorm that opens a layer (or the final one) runs fused into the kernel before it
   auto next_norm = [&](int l) { return l < cfg.n_layers ? w.layers[l].attn_norm : w.final_norm; };
   launch_embed_norm(dt, M, H, V, tokens, w.embed, x, next_norm(0), eps, nbuf, dev_err, s);
+  PendingNorm pn{};
   for (int l = 0; l < cfg.n_layers; ++l) {
     const gm_layer_weights &L = w.layers[l];
     const int sq = launch_gemm("gemm_qkv", dt, EPI_STORE_F32, M, qkv_width(cfg), H, nbuf, H, L.w_qkv, qkv,
-                               qkv_width(cfg), part, s, nullptr, 1.f, true);
+                               qkv_width(cfg), part, s, nullptr, 1.f, true, &pn);
     launch_rope_append(rope_args(cfg, c, l, M, R, qkv, part, sq, q, c.seq_lens, 0, nullptr, 0, L, dev_err), s);
     AttnArgs a = attn_args(cfg, c, l, B, R, c.seq_lens, 0, nullptr);
     a.trace = "attn_verify";
@@ -116,17 +120,20 @@ void run_verify_forward(const gm_model_config &cfg, const gm_model_weights &w, c
     a.out = attn;
     a.dev_err = dev_err;
     run_attention(a, p.attn_plan, ws + p.attn_ws, s);
-    gemm_norm("gemm_o", dt, EPI_ADD_F32, M, H, qd, attn, qd, L.w_o, x, part, L.ffn_norm, eps, nbuf, s);
-    launch_gemm("gemm_gate_up", dt, EPI_SWIGLU, M, F, H, nbuf, H, L.w_gate_up, act, F, part, s);
-    gemm_norm("gemm_down", dt, EPI_ADD_F32, M, H, F, act, F, L.w_down, x, part, next_norm(l + 1), eps, nbuf, s);
+    pn = gemm_norm("gemm_o", dt, EPI_ADD_F32, M, H, qd, attn, qd, L.w_o, x, part, L.ffn_norm, eps, nbuf, s);
+    launch_gemm("gemm_gate_up", dt, EPI_SWIGLU, M, F, H, nbuf, H, L.w_gate_up, act, F, part, s, nullptr, 1.f, false,
+                &pn);
+    pn = gemm_norm("gemm_down", dt, EPI_ADD_F32, M, H, F, act, F, L.w_down, x, part, next_norm(l + 1), eps, nbuf, s);
   }
   if (target_stats) {
     // the rows' softmax statistics in the LM head's epilogue (per tile of ids), then one per row
     RowStat *tiles = (RowStat *)(ws + p.tiles);
-    launch_gemm("gemm_lm_head", dt, EPI_STATS, M, V, H, nbuf, H, w.lm_head, logits, V, part, s, tiles, inv_t);
+    launch_gemm("gemm_lm_head", dt, EPI_STATS, M, V, H, nbuf, H, w.lm_head, logits, V, part, s, tiles, inv_t, false,
+                &pn);
     launch_tile_combine(M, plan_lm_head(dt, M, V, H).tiles, tiles, target_stats, 1, s);
   } else {
-    launch_gemm("gemm_lm_head", dt, EPI_STORE_F32, M, V, H, nbuf, H, w.lm_head, logits, V, part, s);
+    launch_gemm("gemm_lm_head", dt, EPI_STORE_F32, M, V, H, nbuf, H, w.lm_head, logits, V, part, s, nullptr, 1.f, false,
+                &pn);
   }
 }
 
@@ -187,14 +194,15 @@ void run_mtp_draft(const gm_model_config &cfg, const gm_mtp_weights &mtp, const 
   // shared LM head into draft_logits[:, j, :] and the draw of drafts[:, j]
   const float eps = cfg.rms_eps;
   auto tail_and_draw = [&](float *x1, int j) {
-    gemm_norm("mtp_gemm_o", dt, EPI_ADD_F32, B, H, qd, attn_g, qd, L.w_o, x1, part, L.ffn_norm, eps, nbuf, s);
-    launch_gemm("mtp_gemm_gate_up", dt, EPI_SWIGLU, B, F, H, nbuf, H, L.w_gate_up, act, F, part, s);
-    gemm_norm("mtp_gemm_down", dt, EPI_ADD_F32, B, H, F, act, F, L.w_down, x1, part, mtp.final_norm, eps, nbuf, s);
+    PendingNorm pn = gemm_norm("mtp_gemm_o", dt, EPI_ADD_F32, B, H, qd, attn_g, qd, L.w_o, x1, part, L.ffn_norm, eps, nbuf, s);
+    launch_gemm("mtp_gemm_gate_up", dt, EPI_SWIGLU, B, F, H, nbuf, H, L.w_gate_up, act, F, part, s, nullptr, 1.f, false,
+                &pn);
+    pn = gemm_norm("mtp_gemm_down", dt, EPI_ADD_F32, B, H, F, act, F, L.w_down, x1, part, mtp.final_norm, eps, nbuf, s);
     float *zl = draft_logits + (long)j * V;
     // the LM head emits the logits and their softmax statistics per tile of ids; the draw
     // then reads only the tile statistics and one tile of logits per sequence
     launch_gemm("mtp_gemm_lm_head", dt, EPI_STATS, B, V, H, nbuf, H, shared.lm_head, zl, (long)k * V, part, s, tiles,
-                inv_t);
+                inv_t, false, &pn);
     const TileGeom geo = plan_lm_head(dt, B, V, H);
     if (top_p < 1.0) {   // top-p: a draw from each row's nucleus, by the selection or an inverse-CDF scan
       // the nuclei go to the caller's draft_nucleus[:, j] when given (the accept's handoff)
@@ -218,10 +226,10 @@ void run_mtp_draft(const gm_model_config &cfg, const gm_mtp_weights &mtp, const 
   // ---- extend: rows (h_{m+i}, x_{m+i+1}), i = 0..n_b, at slots m_b + i
   launch_mtp_input(dt, Me, H, V, cfg.rms_eps, verify_hidden, out_tokens, 1, shared.embed, mtp.norm_h, mtp.norm_e, u,
                    dev_err, s);
-  gemm_norm("mtp_gemm_proj", dt, EPI_STORE_F32, Me, H, 2 * H, u, 2 * H, mtp.w_proj, x, part, L.attn_norm, eps, nbuf,
+  PendingNorm pn = gemm_norm("mtp_gemm_proj", dt, EPI_STORE_F32, Me, H, 2 * H, u, 2 * H, mtp.w_proj, x, part, L.attn_norm, eps, nbuf,
             s);
   int sq = launch_gemm("mtp_gemm_qkv", dt, EPI_STORE_F32, Me, qw, H, nbuf, H, L.w_qkv, qkv, qw, part, s, nullptr, 1.f,
-                       true);
+                       true, &pn);
   launch_rope_append(rope_args(cfg, c, 0, Me, R, qkv, part, sq, q, lens, 0, n_accept, 1, L, dev_err), s);
   {
     AttnArgs a = attn_args(cfg, c, 0, B, R, lens, 0, n_accept);
@@ -243,10 +251,10 @@ void run_mtp_draft(const gm_model_config &cfg, const gm_mtp_weights &mtp, const 
     if (top_p < 1.0)   // (at top-p 1 the draw of depth j - 1 has built this input)
       launch_mtp_input(dt, B, H, V, cfg.rms_eps, xg, drafts + (j - 1), k, shared.embed, mtp.norm_h, mtp.norm_e, u,
                        dev_err, s);
-    gemm_norm("mtp_gemm_proj", dt, EPI_STORE_F32, B, H, 2 * H, u, 2 * H, mtp.w_proj, xg, part, L.attn_norm, eps, nbuf,
+    pn = gemm_norm("mtp_gemm_proj", dt, EPI_STORE_F32, B, H, 2 * H, u, 2 * H, mtp.w_proj, xg, part, L.attn_norm, eps, nbuf,
               s);
     sq = launch_gemm("mtp_gemm_qkv", dt, EPI_STORE_F32, B, qw, H, nbuf, H, L.w_qkv, qkv, qw, part, s, nullptr, 1.f,
-                     true);
+                     true, &pn);
     launch_rope_append(rope_args(cfg, c, 0, B, 1, qkv, part, sq, q, lens, j - 1, nullptr, 1, L, dev_err), s);
     AttnArgs a = attn_args(cfg, c, 0, B, 1, lens, j - 1, nullptr);
     a.trace = "attn_mtp";
@@ -283,10 +291,10 @@ void run_mtp_reconstruct(const gm_model_config &cfg, const gm_mtp_weights &mtp, 
     else
       launch_mtp_input(dt, R, H, V, eps, xg, drafts + (j - 1), K, shared.embed, mtp.norm_h, mtp.norm_e, u, dev_err,
                        s);
-    gemm_norm("recon_gemm_proj", dt, EPI_STORE_F32, R, H, 2 * H, u, 2 * H, mtp.w_proj, xg, part, L.attn_norm, eps,
+    PendingNorm pn = gemm_norm("recon_gemm_proj", dt, EPI_STORE_F32, R, H, 2 * H, u, 2 * H, mtp.w_proj, xg, part, L.attn_norm, eps,
               nbuf, s);
     const int sq = launch_gemm("recon_gemm_qkv", dt, EPI_STORE_F32, R, qw, H, nbuf, H, L.w_qkv, qkv, qw, part, s,
-                               nullptr, 1.f, true);
+                               nullptr, 1.f, true, &pn);
     launch_rope_append(rope_args(cfg, c, 0, R, 1, qkv, part, sq, q, lens, j, nullptr, 1, L, dev_err), s);
     AttnArgs a = attn_args(cfg, c, 0, R, 1, lens, j, nullptr);
     a.trace = "attn_recon";
@@ -295,11 +303,12 @@ void run_mtp_reconstruct(const gm_model_config &cfg, const gm_mtp_weights &mtp, 
     a.out = attn_g;
     a.dev_err = dev_err;
     run_attention(a, p.attn_chain, ws + p.attn_ws, s);
-    gemm_norm("recon_gemm_o", dt, EPI_ADD_F32, R, H, qd, attn_g, qd, L.w_o, xg, part, L.ffn_norm, eps, nbuf, s);
-    launch_gemm("recon_gemm_gate_up", dt, EPI_SWIGLU, R, F, H, nbuf, H, L.w_gate_up, act, F, part, s);
-    gemm_norm("recon_gemm_down", dt, EPI_ADD_F32, R, H, F, act, F, L.w_down, xg, part, mtp.final_norm, eps, nbuf, s);
+    pn = gemm_norm("recon_gemm_o", dt, EPI_ADD_F32, R, H, qd, attn_g, qd, L.w_o, xg, part, L.ffn_norm, eps, nbuf, s);
+    launch_gemm("recon_gemm_gate_up", dt, EPI_SWIGLU, R, F, H, nbuf, H, L.w_gate_up, act, F, part, s, nullptr, 1.f,
+                false, &pn);
+    pn = gemm_norm("recon_gemm_down", dt, EPI_ADD_F32, R, H, F, act, F, L.w_down, xg, part, mtp.final_norm, eps, nbuf, s);
     launch_gemm("recon_gemm_lm_head", dt, EPI_STORE_F32, R, V, H, nbuf, H, shared.lm_head, head_logits + (long)j * V,
-                (long)K * V, part, s);
+                (long)K * V, part, s, nullptr, 1.f, false, &pn);
   }
 }
 

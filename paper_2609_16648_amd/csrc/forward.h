@@ -63,9 +63,17 @@ GemmPlan plan_gemm(int dtype, int epi, int M, int N, int K);
 // bf16: W pre-tiled (gm.h), X row-major [M][ldx]; `part` must hold plan_gemm().part_bytes.
 // Returns the K splits; with defer_reduce and more than one split, no reduce runs and
 // the partials stay in `part` ([splits][M][Nw] float32) for the consumer to sum.
+// norm (float32 path; x null: none): X [M][K] is yet to be written as RMSNorm(x) * w; the launch
+// normalises on its way in (X then stays as it is) or writes X first.
+struct PendingNorm {
+  const float *x;             // [M][K], or null
+  const void *w;
+  float eps;
+};
 int launch_gemm(const char *name, int dtype, int epi, int M, int N, int K, const void *X, int ldx,
                 const void *W, void *Y, long ldy, float *part, hipStream_t s,
-                RowStat *tile_stats = nullptr, float inv_t = 1.f, bool defer_reduce = false);
+                RowStat *tile_stats = nullptr, float inv_t = 1.f, bool defer_reduce = false,
+                const PendingNorm *norm = nullptr);
 // tile geometry of the softmax statistics an EPI_STATS launch at M rows emits (the draw reads it);
 // *strips_kernel: whether the persistent strip-range kernel runs
 TileGeom plan_lm_head(int dtype, int M, int V, int K, bool *strips_kernel = nullptr);

@@ -397,6 +397,8 @@ struct GemmF {
   float *Y;
   long ldy;
   int M, N, K, ldx;
+  const float *norm_w;   // NORM: X's rows pass through RMSNorm with this weight on their way in
+  float eps;
 };
 
 // float32 products on v_mfma_f32_16x16x4_f32 (float32 multiply-adds throughout).  One
@@ -410,12 +412,16 @@ struct GemmF {
 // the serial chain in each.  One 16 x 16 tile per workgroup with K split over eight waves
 // gives four times the workgroups and an eighth of the chain of a 16 x 64 tile that stages
 // 32 k at a time through LDS (4 x 256 outputs over K = 1024: 70 us there, 4.5 us here).
-template <int EPI, int MT, int NT, int KW>
+//  UB: k groups of 16 loaded together; a wave whose share of K fits in one such batch makes one
+// round trip.  NORM: the rows of X are normalised on their way into the products (the sums and
+// products of rmsnorm_kernel), in place of a launch of its own; the first batch of loads is in
+// flight meanwhile.
+template <int EPI, int MT, int NT, int KW, int UB, bool NORM>
 __global__ __launch_bounds__(64 * KW) void gemm_f32_kernel(GemmF g) {
   constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;   // SwiGLU: the gate columns, then the up columns
-  constexpr int UB = MT * NT == 1 ? 4 : 2;        // k groups of 16 loaded together
   constexpr int TILE = 256 * MT * NT;
   __shared__ float sh[KW][NB * TILE];
+  __shared__ float sh_inv[16 * MT];
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, g4 = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.y * 16 * MT, n0 = blockIdx.x * 16 * NT;
@@ -442,26 +448,48 @@ __global__ __launch_bounds__(64 * KW) void gemm_f32_kernel(GemmF g) {
         for (int t = 0; t < NB * NT; ++t)
           acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[a][q], v[t][q], acc[a][t], 0, 0, 0);
   };
-  int u = u0;
-  for (; u + UB <= u1; u += UB) {                 // all loads of UB groups issued before the first product
-    floatx4u_t x[UB][MT], v[UB][NB * NT];
+  float inv[MT];
+  floatx4u_t x[UB][MT], v[UB][NB * NT], nw[UB];
+  auto load = [&](int u) {       // groups past the share re-read its last one (never multiplied)
 #pragma unroll
     for (int i = 0; i < UB; ++i) {
+      const int k0 = 16 * max(min(u + i, u1 - 1), 0);
 #pragma unroll
-      for (int a = 0; a < MT; ++a) x[i][a] = ld(xp[a] + 16 * (u + i));
+      for (int a = 0; a < MT; ++a) x[i][a] = ld(xp[a] + k0);
 #pragma unroll
-      for (int t = 0; t < NB * NT; ++t) v[i][t] = ld(wp[t] + 16 * (u + i));
+      for (int t = 0; t < NB * NT; ++t) v[i][t] = ld(wp[t] + k0);
+      if (NORM) nw[i] = ld(g.norm_w + k0 + 4 * g4);
     }
+  };
+  load(u0);
+  if (NORM) {
+    for (int r = w; r < 16 * MT; r += KW) {
+      const float *xr = g.X + (long)min(m0 + r, g.M - 1) * g.ldx;
+      float ss = 0.f;
+      for (int c = lane * 4; c < g.K; c += 256) {
+        const floatx4u_t q = ld(xr + c);
+        ss += q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3];
+      }
+      ss = wave_sum(ss);
+      if (lane == 0) sh_inv[r] = 1.0f / sqrtf(ss / (float)g.K + g.eps);
+    }
+    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < UB; ++i) mul(x[i], v[i]);
+    for (int a = 0; a < MT; ++a) inv[a] = sh_inv[16 * a + j];
   }
-  for (; u < u1; ++u) {
-    floatx4u_t x[MT], v[NB * NT];
+  for (int u = u0; u < u1; u += UB) {
+    if (u > u0) load(u);         // all loads of a batch issued before the first product
 #pragma unroll
-    for (int a = 0; a < MT; ++a) x[a] = ld(xp[a] + 16 * u);
+    for (int i = 0; i < UB; ++i) {
+      if (u + i >= u1) break;
+      if (NORM) {
 #pragma unroll
-    for (int t = 0; t < NB * NT; ++t) v[t] = ld(wp[t] + 16 * u);
-    mul(x, v);
+        for (int a = 0; a < MT; ++a)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) x[i][a][q] = x[i][a][q] * inv[a] * nw[i][q];
+      }
+      mul(x[i], v[i]);
+    }
   }
   // lane holds C[row 16a + 4 g4 + r][col 16t + j]
 #pragma unroll
@@ -490,14 +518,28 @@ __global__ __launch_bounds__(64 * KW) void gemm_f32_kernel(GemmF g) {
 }
 
 // 32 x 32 tiles (each loaded operand feeds two products, K split over four waves) where they
-// still give every CU a workgroup, else 16 x 16 tiles and eight waves.
+// still give every CU a workgroup, else 16 x 16 tiles and eight waves, each wave's share of K in
+// one batch of loads up to K = 1024.
+bool f32_small(int M, int N) { return (long)((N + 31) / 32) * ((M + 31) / 32) < 256; }
+
+template <int EPI, bool NORM>
+void launch_f32_small(const GemmF &g, hipStream_t s) {
+  const dim3 grid((g.N + 15) / 16, (g.M + 15) / 16), block(512);
+  const int per = (g.K / 16 + 7) / 8;   // k groups per wave
+  if (per <= 2) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, 1, 8, 2, NORM>), grid, block, 0, s, g);
+  else if (per <= 4) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, 1, 8, 4, NORM>), grid, block, 0, s, g);
+  else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, 1, 8, 8, NORM>), grid, block, 0, s, g);
+}
+
 template <int EPI>
 void launch_f32(const GemmF &g, hipStream_t s) {
-  const long t32 = (long)((g.N + 31) / 32) * ((g.M + 31) / 32);
-  if (t32 >= 256)
-    hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 2, 4>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(256), 0, s, g);
+  if (!f32_small(g.M, g.N))
+    hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 2, 4, 2, false>), dim3((g.N + 31) / 32, (g.M + 31) / 32), dim3(256), 0,
+                       s, g);
+  else if (g.norm_w)
+    launch_f32_small<EPI, true>(g, s);
   else
-    hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, 1, 8>), dim3((g.N + 15) / 16, (g.M + 15) / 16), dim3(512), 0, s, g);
+    launch_f32_small<EPI, false>(g, s);
 }
 
 // ------------------------------------------------------------------ LM head, M <= 64
@@ -871,7 +913,8 @@ TileGeom plan_lm_head(int dtype, int M, int V, int K, bool *strips_kernel) {
 }
 
 int launch_gemm(const char *name, int dtype, int epi, int M, int N, int K, const void *X, int ldx, const void *W,
-                void *Y, long ldy, float *part, hipStream_t s, RowStat *tile_stats, float inv_t, bool defer_reduce) {
+                void *Y, long ldy, float *part, hipStream_t s, RowStat *tile_stats, float inv_t, bool defer_reduce,
+                const PendingNorm *norm) {
   if (M <= 0) return 1;
   // The LM head at M <= 64, with statistics or without, takes the strip ranges: a verify layer with
   // LM head at 4 / 16 / 32 / 64 rows 198.6 / 205 / 214 / 227 us against 198.9 / 214 / 232 / 257 with the
@@ -915,7 +958,19 @@ int launch_gemm(const char *name, int dtype, int epi, int M, int N, int K, const
     }
     return 1;
   } else {
-    GemmF g{(const float *)X, (const float *)W, (float *)Y, ldy, M, N, K, ldx};
+    GemmF g{(const float *)X, (const float *)W, (float *)Y, ldy, M, N, K, ldx, nullptr, 0.f};
+    if (norm && norm->x) {
+      // the norm of X's rows, left to this launch: inside it where each column tile holds few rows
+      // (a launch fewer; 4 x 256 outputs over K = 256 read 16 rows more), else a pass before it
+      if (f32_small(M, N)) {
+        g.X = norm->x;
+        g.ldx = K;
+        g.norm_w = (const float *)norm->w;
+        g.eps = norm->eps;
+      } else {
+        launch_rmsnorm(dtype, M, K, norm->eps, norm->x, norm->w, (void *)X, s);
+      }
+    }
     if (epi == EPI_STATS) {     // no fused epilogue on this path: a pass over the output rows
       {
         TraceScope ts(name, s);
