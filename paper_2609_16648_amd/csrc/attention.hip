@@ -277,10 +277,11 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
   float m[RT], l[RT];
   floatx4_t O[RT][8];
   // The end of a segment.  A sequence that lies wholly in this range is normalised and written
-  // as it is (the combine skips it); a part of one goes to the partials.  The rows pass through
-  // this wave's slice of LDS so that every store covers whole lines: stores of the 16 or 64
-  // bytes a lane group holds of a row, for padding rows too, held the KV stream up by 25 us per
-  // segment (1024 sequences of 2560 tokens: 1784 us with them, 1598 us here).
+  // as it is (the combine skips it), its rows through this wave's slice of LDS so that a store
+  // covers whole lines; a part of one goes to the partials, past the caches.  Ordinary stores
+  // of the partials of every sequence, padding rows too, held the KV stream up by 25 us per
+  // segment (1024 sequences of 2560 tokens: 1784 us with them, 1598 us here); the partials
+  // through LDS as well cost short ranges 1.5 us and long ones as much as they saved.
   extern __shared__ __attribute__((aligned(16))) float attn_sh[];   // kAttnLdsReserve bytes
   float *const rows_sh = attn_sh + w * 16 * kAttnRowPad;
   auto finish = [&]() __attribute__((always_inline)) {
@@ -290,41 +291,37 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
       float lu = l[u];
       lu += __shfl_xor(lu, 16, kWave);
       lu += __shfl_xor(lu, 32, kWave);
-      const long prow0 = ((long)(part + b) * a.n_kv + kvh) * a.rows_pad + (rt0 + u) * 16;
-      if (!whole && g == 0) a.part_ml[prow0 + j] = make_float2(m[u], lu);
+      if (!whole) {
+        const long prow = ((long)(part + b) * a.n_kv + kvh) * a.rows_pad + (rt0 + u) * 16 + j;
+        if (g == 0) a.part_ml[prow] = make_float2(m[u], lu);
+        if ((rt0 + u) * 16 + j < rows) {
+#pragma unroll
+          for (int mm = 0; mm < 8; ++mm)
+            __builtin_nontemporal_store(O[u][mm], reinterpret_cast<floatx4_t *>(a.part_o + prow * 128 + 16 * mm + 4 * g));
+        }
+        continue;
+      }
       // rows with no visible token (past the block, or none readable) give 0
       const bool live = vis[u] > 0 && m[u] != -INFINITY;
       const float inv = 1.f / lu;
       wave_lds_sync();
 #pragma unroll
-      for (int mm = 0; mm < 8; ++mm) {
-        floatx4_t v = O[u][mm];
-        if (whole) v = live ? v * inv : floatx4_t{0.f, 0.f, 0.f, 0.f};
-        *reinterpret_cast<floatx4_t *>(rows_sh + j * kAttnRowPad + 16 * mm + 4 * g) = v;
-      }
+      for (int mm = 0; mm < 8; ++mm)
+        *reinterpret_cast<floatx4_t *>(rows_sh + j * kAttnRowPad + 16 * mm + 4 * g) =
+            live ? O[u][mm] * inv : floatx4_t{0.f, 0.f, 0.f, 0.f};
       wave_lds_sync();
       const int nr = min(16, rows - (rt0 + u) * 16);   // rows of this tile that exist
-      if (whole) {
 #pragma unroll 1   // (the segment's end is inlined at every ring position: short code counts here)
-        for (int q = 0; q < 4; ++q) {
-          const int rl = 4 * q + g, r = (rt0 + u) * 16 + rl;
-          if (rl >= nr) continue;
-          const float *src = rows_sh + rl * kAttnRowPad + 8 * j;
-          uint32_t pk[4];
+      for (int q = 0; q < 4; ++q) {
+        const int rl = 4 * q + g, r = (rt0 + u) * 16 + rl;
+        if (rl >= nr) continue;
+        const float *src = rows_sh + rl * kAttnRowPad + 8 * j;
+        uint32_t pk[4];
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-            pk[c] = f32_to_bf16(src[2 * c]) | (uint32_t(f32_to_bf16(src[2 * c + 1])) << 16);
-          const long o = (((long)b * a.R + r % a.R) * a.n_heads + kvh * a.G + r / a.R) * 128 + 8 * j;
-          *reinterpret_cast<uint4 *>(a.out + o) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-        }
-      } else {
-#pragma unroll 2
-        for (int q = 0; q < 8; ++q) {
-          const int rl = 2 * q + (lane >> 5), c = 4 * (lane & 31);
-          if (rl < nr)
-            *reinterpret_cast<floatx4_t *>(a.part_o + (prow0 + rl) * 128 + c) =
-                *reinterpret_cast<const floatx4_t *>(rows_sh + rl * kAttnRowPad + c);
-        }
+        for (int c = 0; c < 4; ++c)
+          pk[c] = f32_to_bf16(src[2 * c]) | (uint32_t(f32_to_bf16(src[2 * c + 1])) << 16);
+        const long o = (((long)b * a.R + r % a.R) * a.n_heads + kvh * a.G + r / a.R) * 128 + 8 * j;
+        *reinterpret_cast<uint4 *>(a.out + o) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
       }
     }
   };
