@@ -25,6 +25,9 @@ struct DcaRow {          // per (cycle, position): what the gradient pass needs
   int g_rest, pad;
 };
 constexpr int kDcaIds = 4096;   // ids per block of the gradient pass
+// Gradients of this size and more are stored past the caches (1.9 GB: 2% off the launch); smaller
+// ones stay in the 256 MB last-level cache (62 MB: 48 us past it, 43 through it)
+constexpr size_t kDcaStreamBytes = size_t(256) << 20;
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -105,9 +108,9 @@ __global__ __launch_bounds__(1024) void dca_cycle_kernel(int K, int V, int topk,
 // nch blocks of kDcaIds ids per row, neighbouring blocks on neighbouring ids.  A row past the first rejection has
 // coefficient 0: its gradient is written without reading its logits (a quarter of the rows
 // with accepted lengths uniform in 0..3).  All loads of a thread are issued before the first
-// exponential; the gradient is written past the caches.  1024 cycles x 3 x 151936 ids:
+// exponential; large gradients are written past the caches.  1024 cycles x 3 x 151936 ids:
 // 583 us, against 767 with every row read, one load in flight per thread and ordinary stores.
-__global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch, const float *__restrict__ z,
+__global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch, bool stream, const float *__restrict__ z,
                                                        const DcaRow *__restrict__ rows,
                                                        const int32_t *__restrict__ rec_ids,
                                                        const uint8_t *__restrict__ flags, float *__restrict__ grad) {
@@ -120,6 +123,18 @@ __global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch,
   float *gr = grad + r * V;
   const bool vec = (V & 3) == 0 && ((reinterpret_cast<uintptr_t>(z) | reinterpret_cast<uintptr_t>(grad)) & 15) == 0;
   const bool zero = d.coef == 0.0;
+  // the record's ids in this range carry their own flags; read beside the row's logits
+  int own_id = -1;
+  if (!zero && (int)threadIdx.x < topk) own_id = rec_ids[r * topk + threadIdx.x];
+  float own_z = 0.f;
+  int own_flag = 0;
+  auto load_own = [&]() {
+    if (own_id < lo || own_id >= hi) own_id = -1;
+    if (own_id >= 0) {
+      own_z = zr[own_id];
+      own_flag = flags[r * topk + threadIdx.x];
+    }
+  };
   if (vec) {
     constexpr int kVec = kDcaIds / (4 * 256);
     floatx4_t v[kVec];
@@ -128,6 +143,7 @@ __global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch,
       const int x = lo + 4 * ((int)threadIdx.x + 256 * u);
       v[u] = !zero && x < hi ? *reinterpret_cast<const floatx4_t *>(zr + x) : floatx4_t{0.f, 0.f, 0.f, 0.f};
     }
+    load_own();
 #pragma unroll
     for (int u = 0; u < kVec; ++u) {
       const int x = lo + 4 * ((int)threadIdx.x + 256 * u);
@@ -137,23 +153,19 @@ __global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch,
 #pragma unroll
         for (int q = 0; q < 4; ++q) o[q] = coef * (expf(v[u][q] - M) * inv_s) * rest;
       }
-      __builtin_nontemporal_store(o, reinterpret_cast<floatx4_t *>(gr + x));
+      if (stream) __builtin_nontemporal_store(o, reinterpret_cast<floatx4_t *>(gr + x));
+      else *reinterpret_cast<floatx4_t *>(gr + x) = o;
     }
   } else {
+    load_own();
     for (int x = lo + (int)threadIdx.x; x < hi; x += blockDim.x)
       gr[x] = zero ? 0.f : coef * (expf(zr[x] - M) * inv_s) * rest;
   }
-  if (zero) return;
-  // the record's ids in this range carry their own flags: rewritten once the stores above are done
+  // written over the rest's once the stores above are done
+  if (!__syncthreads_or(own_id >= 0)) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if ((int)threadIdx.x < topk) {
-    const int id = rec_ids[r * topk + threadIdx.x];
-    if (id >= lo && id < hi) {
-      const float own = (float)((double)flags[r * topk + threadIdx.x] - d.gbar);
-      gr[id] = coef * (expf(zr[id] - M) * inv_s) * own;
-    }
-  }
+  if (own_id >= 0) gr[own_id] = coef * (expf(own_z - M) * inv_s) * (float)((double)own_flag - d.gbar);
 }
 }  // namespace
 
@@ -181,8 +193,8 @@ void run_dca_loss(int N, int K, int V, int topk, const float *head_logits, const
   if (grad) {
     TraceScope ts("dca_grad", s);
     const int nch = (V + kDcaIds - 1) / kDcaIds;
-    hipLaunchKernelGGL(dca_grad_kernel, dim3((unsigned)N * K * nch), dim3(256), 0, s, V, topk, nch, head_logits, rows,
-                       rec_ids, flags, grad);
+    hipLaunchKernelGGL(dca_grad_kernel, dim3((unsigned)N * K * nch), dim3(256), 0, s, V, topk, nch,
+                       (size_t)N * K * V * sizeof(float) >= kDcaStreamBytes, head_logits, rows, rec_ids, flags, grad);
   }
 }
 
