@@ -601,7 +601,8 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnF a) {
       }
     }
     const float mn = fmaxf(m, wave_max(sc));
-    if (mn == -INFINITY) continue;   // no readable token in the chunk
+    // no readable token in the chunk (the maximum passes NaN scores over: they have to reach the row)
+    if (mn == -INFINITY && !__any(sc != sc)) continue;
     const float p = expf(sc - mn), al = expf(m - mn);
     l = l * al + wave_sum(p);
     m = mn;
@@ -645,7 +646,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnF a) {
     float den = 0.f, num = 0.f;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (sh_m[u] == -INFINITY) continue;
+      if (sh_l[u] == 0.f) continue;   // the wave read no token
       const float f = expf(sh_m[u] - M);
       den += sh_l[u] * f;
       num += sh_o[u][tid] * f;

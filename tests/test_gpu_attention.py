@@ -119,6 +119,26 @@ def test_f32_attention_chunk_edges(head_dim, n_kv, page_size, lens, k):
     assert rel_err(got, ref) < 2e-5
 
 
+@pytest.mark.parametrize("bad", [(0, 64), (64, 128), (5, 6), (0, 202)])   # whole chunks of a wave, one token, all
+def test_f32_attention_nan_scores_reach_the_row(bad):
+    need_gpu()
+    shape, lens, R = synth.TINY, np.array([200]), 2
+    ctx = lens + R
+    ks, vs = synth.kv_prefix(shape, ctx, layer=9, seed=2)
+    ks[0] = np.array(ks[0])
+    ks[0][bad[0]:bad[1], 1] = np.nan                # head 1 only
+    q = synth.normal_tensor((1, R, shape.n_heads, shape.head_dim), 5, shape.dtype, "q-nan")
+    cache = gm.PagedCache(shape, 1, lens, ctx, page_size=16, fill="empty")
+    cache.write(0, 0, np.arange(ctx[0]), ks[0], vs[0])
+    out = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+    gm.verify_attention(gm.model_config(shape), cache, 0, t32(q), out, gm.Workspace())
+    torch.cuda.synchronize()
+    ref = oracle.attention(q[0].astype(np.float64), ks[0].astype(np.float64), vs[0].astype(np.float64),
+                           lens[0] + np.arange(R) + 1)
+    assert np.isnan(ref[:, 1]).all() and np.isfinite(ref[:, [0, 2, 3]]).all()
+    np.testing.assert_allclose(out[0].cpu().numpy(), ref, rtol=0, atol=2e-5 * np.abs(ref[:, 0]).max())
+
+
 def test_gqa_group_of_eight_and_odd_rows():
     # 32 query heads on 4 KV heads with k = 2: 24 rows in two 16-row tiles
     need_gpu()
