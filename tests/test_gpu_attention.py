@@ -124,6 +124,14 @@ def test_bf16_attention_sequences_after_a_window():
             assert _row_err(oracle.attention(q, k[lost], v[lost], vis - 16), ref) > 2 * LONG_TOL
 
 
+@pytest.mark.parametrize("tiles", [1, 2, 3, 4, 5, 6, 7, 8, 127, 129, 256, 257, 258, 260])
+def test_bf16_attention_tiles_per_range(tiles):
+    # the ring's turns and the tiles behind them, at every remainder, and windows of one to four tiles
+    need_gpu()
+    for got, q, k, v, vis in _long_case([16 * 25 * tiles - 2], 1, [5, 38]):
+        assert _row_err(got, oracle.attention(q, k, v, vis)) < LONG_TOL
+
+
 def test_f32_attention_matches_oracle():
     need_gpu()
     shape = synth.TINY
