@@ -818,10 +818,12 @@ void run_attention(const AttnArgs &a, const AttnPlan &p, char *ws, hipStream_t s
     }
     TraceScope ts(a.trace_combine, s);
     const int out_rows = a.n_kv * G * a.R;
-    // more than a batch of partials per sequence, and few enough rows that a workgroup for each costs
-    // less than the round trips it saves (one row per sequence: 7 sequences in 18 partials each 13.6 ->
-    // 7.6 us; 16 sequences of 128 rows in 8 partials: 14 us slower with a workgroup per row)
-    if (p.parts >= 8 * a.B && (long)out_rows * a.B <= 512)
+    // Sixteen groups per row save a round trip per eight partials of a sequence and cost a workgroup per
+    // row: taken where a sequence has more than a batch of partials and the launch at most 32 rows per
+    // partial of a sequence.  (Rows, partials: attention and combine with one group -> sixteen, us.
+    // 512, 32: 20.0 -> 16.3; 672, 43: 27.1 -> 21.8; 800, 26: 44.1 -> 42.5; 1024, 32: 28.0 -> 26.9;
+    // 672, 18: 18.6 -> 18.8; 1024, 16: 18.6 -> 20.1; 1344, 18: 23.1 -> 26.4; 2048, 8: 21.0 -> 30.5.)
+    if (p.parts >= 8 * a.B && (long)out_rows * a.B * a.B <= 32L * p.parts)
       hipLaunchKernelGGL(attn_combine_kernel<16>, dim3(out_rows, a.B), dim3(512), 0, s, k);
     else
       hipLaunchKernelGGL(attn_combine_kernel<1>, dim3((out_rows + 7) / 8, a.B), dim3(256), 0, s, k);
