@@ -46,6 +46,12 @@ constexpr int kAttnRowPad = 132;        // floats between rows of an output tile
 static_assert(kAttnWavesPerGroup * 16 * kAttnRowPad * 4 <= kAttnLdsReserve, "the waves' slices fit the reservation");
 constexpr int kAttnRing = 3;            // K/V register buffers per wave
 constexpr float kLazyLog2 = 8.f;        // rescale threshold of the running max (log2 units)
+// Ranges of this many tiles store the partials of cut sequences through the caches, shorter and longer
+// ones past them (attention and combine, us, past the caches -> through them, by tiles per range:
+// 0.6: 18.4 -> 19.2 and 18.3 -> 20.1; 2.5: 22.1 -> 24.4 and 17.6 -> 19.8; 6.5: 21.4 -> 20.5; 10.5: 42.4 -> 38.1;
+// 16: 36.7 -> 35.5; 80: 120.9 -> 118.6; 94: 133.2 -> 131.9; 117: 168.2 -> 168.2; 384: 496.5 -> 499.9;
+// 576: 750 -> 775).
+constexpr int kPartCachedTiles = 4, kPartStreamTiles = 128;
 
 struct AttnK {
   const uint16_t *kp, *vp;
@@ -279,13 +285,14 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
   floatx4_t O[RT][8];
   // The end of a segment.  A sequence that lies wholly in this range is normalised and written
   // as it is (the combine skips it), its rows through this wave's slice of LDS so that a store
-  // covers whole lines; a part of one goes to the partials, past the caches.  Ordinary stores
-  // of the partials of every sequence, padding rows too, held the KV stream up by 25 us per
-  // segment (1024 sequences of 2560 tokens: 1784 us with them, 1598 us here); the partials
-  // through LDS as well cost short ranges 1.5 us and long ones as much as they saved.
+  // covers whole lines; a part of one goes to the partials (kPartCachedTiles).  Storing the
+  // partials of every sequence, padding rows too, held the KV stream up by 25 us per segment
+  // (1024 sequences of 2560 tokens: 1784 us so, 1598 us with whole sequences written directly);
+  // the partials through LDS as well cost short ranges 1.5 us and long ones as much as they saved.
   extern __shared__ __attribute__((aligned(16))) float attn_sh[];   // kAttnLdsReserve bytes
   float *const rows_sh = attn_sh + w * 16 * kAttnRowPad;
   auto finish = [&]() __attribute__((always_inline)) {
+    const bool cached = e - s >= kPartCachedTiles && e - s < kPartStreamTiles;
     const bool whole = cb >= s && seq_end <= e;
 #pragma unroll
     for (int u = 0; u < RT; ++u) {
@@ -296,9 +303,16 @@ __global__ __launch_bounds__(64 * kAttnWavesPerGroup) void attn_mfma_kernel(Attn
         const long prow = ((long)(part + b) * a.n_kv + kvh) * a.rows_pad + (rt0 + u) * 16 + j;
         if (g == 0) a.part_ml[prow] = make_float2(m[u], lu);
         if ((rt0 + u) * 16 + j < rows) {
+          floatx4_t *const dst = reinterpret_cast<floatx4_t *>(a.part_o + prow * 128 + 4 * g);
+          if (cached) {
+            asm volatile("" ::: "memory");   // (stores that differ in the hint alone would be merged)
 #pragma unroll
-          for (int mm = 0; mm < 8; ++mm)
-            __builtin_nontemporal_store(O[u][mm], reinterpret_cast<floatx4_t *>(a.part_o + prow * 128 + 16 * mm + 4 * g));
+            for (int mm = 0; mm < 8; ++mm) dst[4 * mm] = O[u][mm];
+            asm volatile("" ::: "memory");
+          } else {
+#pragma unroll
+            for (int mm = 0; mm < 8; ++mm) __builtin_nontemporal_store(O[u][mm], dst + 4 * mm);
+          }
         }
         continue;
       }
