@@ -126,6 +126,21 @@ void launch_accept_decide(int B, int k, int V, int mode, float inv_t, double inv
 constexpr int kNucSplitRows = 256;     // rows x workgroups per row of a split first pass
 constexpr int kNucMaxSplit = 16;
 constexpr size_t kNucPartBytes = (size_t)kNucSplitRows * 4096 * 8;
+// Workgroups that share the first pass over a row (1: not split), each on at least kNucSliceIds ids.
+// Rows with fewer ids than the rows leave workgroups for are cut into as many slices as they give, from
+// eight on (accepts of 1-5 sequences, us, unsplit -> split: 50257 ids in 12 slices 83.4 -> 81.0 and 92.7 ->
+// 87.5; 32001 in 7 72.8 -> 77.4; 20000 in 4 60.9 -> 69.3; 10000 in 2 58.7 -> 71.5).
+constexpr int kNucSliceIds = 4096, kNucMinSlices = 8;
+constexpr int nucleus_splits(int n_rows, int V) {
+  int S = kNucSplitRows / n_rows;
+  if (S > kNucMaxSplit) S = kNucMaxSplit;
+  if (V < S * kNucSliceIds) S = V / kNucSliceIds < kNucMinSlices ? 1 : V / kNucSliceIds;
+  return S < 2 ? 1 : S;
+}
+static_assert(nucleus_splits(1, 151936) == 16 && nucleus_splits(16, 50257) == 12 && nucleus_splits(19, 50257) == 12 &&
+                  nucleus_splits(1, 32768) == 8 && nucleus_splits(1, 32001) == 1 && nucleus_splits(100, 8192) == 2 &&
+                  nucleus_splits(129, 151936) == 1,
+              "few rows are split as far as their ids go");
 // draw (may be null): also a draw from row r's nucleus with u[r * u_stride], made into dst[r * dst_stride]
 // where the nucleus was found among few ids (sel[r].active = 0), else left in sel[r] for launch_residual_draw
 struct NucDraw {

@@ -1264,10 +1264,8 @@ void launch_nucleus(const char *name, int n_rows, int V, double inv_td, double t
                     unsigned long long *part, hipStream_t s, const NucDraw *draw) {
   if (n_rows <= 0) return;
   TraceScope ts(name, s);
-  // fewer than 128 rows leave CUs idle: their first pass is split over up to kNucMaxSplit workgroups per row
-  int S = part ? kNucSplitRows / n_rows : 1;
-  if (S > kNucMaxSplit) S = kNucMaxSplit;
-  if (S < 2 || V < S * 4096) S = 1;
+  // up to 128 rows leave CUs idle: their first pass is split over up to kNucMaxSplit workgroups per row
+  const int S = part ? nucleus_splits(n_rows, V) : 1;
   if (S > 1)
     hipLaunchKernelGGL(nucleus_hist_kernel, dim3(n_rows * S), dim3(kNucThreads), 0, s, V, inv_td, top_p, logits,
                        row_stride, st, nch, S, part);

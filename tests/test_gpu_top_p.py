@@ -74,7 +74,12 @@ def _logits(shape, kind, *tags):
     (8, 2, 151936, 1.0, 0.5, "flat"),          # too many ties for LDS: the passes over the row
     (3, 0, 5000, 1.0, 0.7, "normal"),          # no drafts: the bonus draw from the target's nucleus
     (16, 2, 1001, 1.0, 0.6, "normal"),         # rows not a multiple of 4 ids: unaligned row reads
-    (1, 1, 151936, 1.0, 0.7, "normal"),        # one sequence: the first pass split over 8 workgroups
+    (1, 1, 151936, 1.0, 0.7, "normal"),        # one sequence: the first pass split over 16 workgroups
+    # few rows of a middle vocabulary: split as far as its ids go, in 12 slices off 16-byte boundaries
+    (4, 3, 50257, 1.0, 0.7, "normal"),
+    (6, 1, 50257, 1.0, 0.7, "peaked"),
+    (1, 2, 50257, 1.0, 0.95, "wide"),
+    (2, 1, 32768, 1.0, 0.7, "peaked"),         # the least number of ids that is cut into eight slices
     # a head close to the target (zq = zt + 0.1 N(0, 1)): most drafts accepted, so the deep
     # prefixes and the bonus draw from the last target row's nucleus are compared
     # peaked rows, queued in one pass: ranked by counting, by the radix selection over the queue, too
