@@ -863,6 +863,26 @@ __device__ __forceinline__ int nuc_band(double y) {   // y >= -32; grows with y
   return kNucBands - 1 - (b < 0 ? 0 : b < kNucBands ? b : kNucBands - 1);
 }
 
+// sums of two values per thread over the block; wtot >= 32 entries.  Holds barriers.
+__device__ __forceinline__ void block_sums_u64(unsigned long long &a, unsigned long long &b, unsigned long long *wtot) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o, kWave);
+    b += __shfl_xor(b, o, kWave);
+  }
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) {
+    wtot[threadIdx.x >> 6] = a;
+    wtot[16 + (threadIdx.x >> 6)] = b;
+  }
+  __syncthreads();
+  a = b = 0;
+  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+    a += wtot[w];
+    b += wtot[16 + w];
+  }
+}
+
 // sum of one value per thread over the block; wtot >= 16 entries.  Holds barriers.
 __device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v, unsigned long long *wtot) {
 #pragma unroll
@@ -964,7 +984,7 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
   __shared__ float qv[kNucQueue];
   __shared__ int qx[kNucQueue];
   __shared__ unsigned sh_qn;
-  __shared__ unsigned long long wtot[kNucThreads / 64];
+  __shared__ unsigned long long wtot[2 * (kNucThreads / 64)];
   __shared__ float red_m[kNucThreads / 64];
   __shared__ int red_a[kNucThreads / 64];
   __shared__ int sh_bin, sh_idt;
@@ -994,25 +1014,23 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
   unsigned qn = 0;
   bool queued = false;   // the boundary is among the queued ids
   if (peaked) {
-    unsigned long long t = 0;
+    unsigned long long t = 0, q = 0;   // masses: the row's, the queued ids'
     if (part) {
       const unsigned long long *src = part + (long)r * S * kNucBins;
-      for (int sg = 0; sg < S; ++sg) {
+      // a wave per slice: the slices' counts, then their ids, are read at once
+      const int lane = tid & 63;
+      for (int sg = tid >> 6; sg < S; sg += kNucThreads / 64) {
         const unsigned long long n = src[(long)sg * kNucBins + 1];
-        if (tid == 0) {
+        if (lane == 0) {
           t += src[(long)sg * kNucBins];
           if (n > kNucSliceMax) atomicAdd(&sh_qn, (unsigned)kNucQueue + 1u);   // ids are missing: not queued
         }
-        for (unsigned i = tid; i < (unsigned)n && i < (unsigned)kNucSliceMax; i += kNucThreads) {
+        for (unsigned i = lane; i < (unsigned)n && i < (unsigned)kNucSliceMax; i += 64) {
           const unsigned long long c = src[(long)sg * kNucBins + 2 + kNucBands + i];
-          push(__uint_as_float((uint32_t)(c >> 32)), (int)(uint32_t)c);
+          const float v = __uint_as_float((uint32_t)(c >> 32));
+          q += nuc_mass(v, inv_td, m, etab);
+          push(v, (int)(uint32_t)c);
         }
-      }
-      for (int b = tid; b < kNucBands; b += kNucThreads) {
-        unsigned long long h = 0;
-#pragma unroll 8
-        for (int sg = 0; sg < S; ++sg) h += src[(long)sg * kNucBins + 2 + b];
-        hist[b] = h;
       }
     } else {
       const double cut = nuc_cut(S_row, top_p), guard = nuc_guard(S_row, top_p, V);
@@ -1021,18 +1039,17 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
         const unsigned long long e = nuc_mass(v, inv_td, m, etab, y);
         t += e;
         if (y >= guard) atomicAdd(&hist[nuc_band(y)], e);
-        if (y >= cut) push(v, x);
+        if (y >= cut) {
+          q += e;
+          push(v, x);
+        }
       });
     }
-    tot = block_sum_u64(t, wtot);
+    block_sums_u64(t, q, wtot);
+    tot = t;
     thr = top_p * (double)tot;
     qn = sh_qn;
-    if (qn <= (unsigned)kNucQueue) {
-      unsigned long long q = 0;
-      for (unsigned i = tid; i < qn; i += kNucThreads) q += nuc_mass(qv[i], inv_td, m, etab);
-      q = block_sum_u64(q, wtot);
-      queued = tot > 0 && (double)q >= thr;
-    }
+    queued = qn <= (unsigned)kNucQueue && tot > 0 && (double)q >= thr;
     if (queued && qn <= (unsigned)kNucRank) {
       // few: each id's running mass is the mass of the ids ranked before it; the boundary is the
       // id whose own mass takes it to thr, and the ids of equal logit past it are left out.  The
@@ -1089,13 +1106,21 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
       }
       return;
     }
-    if (!queued && tot > 0) {
+    if (!queued && tot > 0 && top_p > kNucBandTopP) {
       // the boundary's band, then its ids from the row
-      unsigned long long h = 0;
-      for (int b = tid; b < kNucBands; b += kNucThreads) h += hist[b];
-      h = block_sum_u64(h, wtot);
-      if ((double)h >= thr) {
-        nuc_find_bin(hist, kNucBands, 0ull, thr, wtot, &sh_bin, &sh_above);
+      if (part) {
+        const unsigned long long *src = part + (long)r * S * kNucBins;
+        for (int b = tid; b < kNucBands; b += kNucThreads) {
+          unsigned long long h = 0;
+#pragma unroll 8
+          for (int sg = 0; sg < S; ++sg) h += src[(long)sg * kNucBins + 2 + b];
+          hist[b] = h;
+        }
+      }
+      if (tid == 0) sh_bin = -1;
+      __syncthreads();
+      nuc_find_bin(hist, kNucBands, 0ull, thr, wtot, &sh_bin, &sh_above);
+      if (sh_bin >= 0) {
         const int band = sh_bin;
         above = sh_above;
         if (tid == 0) sh_qn = 0u;

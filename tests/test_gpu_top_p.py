@@ -200,6 +200,83 @@ def test_top_p_nucleus_handoff():
     print("[top-p handoff] mean accepted %.2f" % res[0][0].mean(), flush=True)
 
 
+def _head_rows(kinds, B, V, top_p):
+    """Logits rows of a confident head, one id holding most of the mass over a floor N(0, 1) (kind, the
+    floor's share of the mass), cycling through the kinds."""
+    g = synth.stream(3, "head-rows", B, V, top_p)
+    rows = np.empty((B, V), np.float32)
+    for b in range(B):
+        kind, share = kinds[b % len(kinds)]
+        r = g.standard_normal(V)
+        if kind == "dense":        # the whole floor within a sixteenth of an exponent
+            r *= 0.005
+        elif kind.startswith("ties"):
+            n = float(kind[4:])
+            r = np.round(r * n) / n
+        r[g.integers(0, V)] = np.log(np.exp(r).sum() * (1.0 - share) / share)
+        rows[b] = r
+    return rows
+
+
+@pytest.mark.parametrize("B,V,top_p", [(16, 151936, 0.95), (16, 50257, 0.85), (136, 20000, 0.95), (130, 50256, 0.99)])
+def test_top_p_nuclei_of_chosen_rows(B, V, top_p):
+    # The nuclei that gm_mtp_draft hands over, id by id, for boundaries among ids too unlikely to be queued:
+    # found through the bands of the exponent and gathered ("floor"; with runs of ties ranked in LDS,
+    # "ties64", and past that, "ties8"), in a band that overflows the gather ("dense"), and among the queued
+    # ids (a floor of a tenth of 1 - top_p).  The first pass is split over blocks in the first two cases.
+    # The head passes row b's logits through: a one-hot hidden selects column b of the LM head.
+    need_gpu()
+    import dataclasses
+    from helpers import device_cache
+    rest = 1.0 - top_p
+    kinds = [("floor", 6 * rest), ("ties64", 5 * rest), ("ties8", 6 * rest), ("dense", 4 * rest), ("floor", 0.1 * rest),
+             ("floor", 1.3 * rest)]
+    shape = dataclasses.replace(synth.TINY, vocab=V)
+    H, k = shape.hidden, 1
+    rows = _head_rows(kinds, B, V, top_p)
+    lm = np.zeros((V, H), np.float32)
+    lm[:, :B] = rows.T / np.float32(16.0)              # RMSNorm of a one-hot of H = 256 channels is 16 at it
+    W = dict(embed=np.zeros((V, H), np.float32), final_norm=np.ones(H, np.float32), lm_head=lm, layers=[])
+    Wm = dict(synth.mtp_weights(shape))
+    Wm["w_proj"] = np.concatenate([np.eye(H, dtype=np.float32), np.zeros((H, H), np.float32)], 1)
+    Wm["layer"] = dict(Wm["layer"], wo=np.zeros_like(Wm["layer"]["wo"]), w_down=np.zeros_like(Wm["layer"]["w_down"]))
+    lens = np.ones(B, np.int64)
+    cache = device_cache(shape, [synth.kv_prefix(shape, lens, layer=7)], lens, 2 * k + 2)
+    hidden = np.zeros((B, k + 1, H), np.float32)
+    hidden[np.arange(B), :, np.arange(B)] = 1.0
+    u = synth.uniforms(B, k, 4, "head-rows", V)[2]
+    drafts = torch.zeros((B, k), dtype=torch.int32, device="cuda")
+    dlog = torch.zeros((B, k, V), dtype=torch.float32, device="cuda")
+    nuc = gm.new_nuclei(B, k)
+    gm.mtp_draft(gm.DeviceModel(shape, W), gm.DeviceMtp(shape, Wm), cache, k, gm.GM_SAMPLE, t32(hidden),
+                 i32(np.zeros(B)), i32(np.zeros((B, k + 1))), t32(u), drafts, dlog, gm.Workspace(), top_p=top_p,
+                 draft_nucleus=nuc)
+    torch.cuda.synchronize()
+    z, h, x = dlog.cpu().numpy()[:, 0], nuc.cpu().numpy()[:, 0], drafts.cpu().numpy()[:, 0]
+    assert np.abs(z - rows).max() < 1e-5
+    m, mass = (h[:, o:o + 8].copy().view(np.float64)[:, 0] for o in (0, 8))
+    key, last = h[:, 16:20].copy().view(np.uint32)[:, 0], h[:, 20:24].copy().view(np.int32)[:, 0]
+    flagged = 0
+    for b in range(B):
+        kind, share = kinds[b % len(kinds)]
+        p = oracle.softmax(z[b].astype(np.float64))
+        # the inputs meet the paths they are meant for (the selection queues ids above rest / 2048 of the mass)
+        assert (p[p > rest / 2048].sum() < top_p) == (share > rest), (b, kind, share)
+        kept, dist = oracle.nucleus(z[b], p, top_p)
+        if dist < NUC_EPS:
+            flagged += 1
+            continue
+        bits = z[b].view(np.uint32)
+        okey = np.where(bits == 0x80000000, np.uint32(0x80000000),
+                        np.where(bits & 0x80000000, ~bits, bits | 0x80000000)).astype(np.uint32)
+        got = (okey > key[b]) | ((okey == key[b]) & (np.arange(V) <= last[b]))
+        np.testing.assert_array_equal(got, kept > 0, err_msg="%d %s" % (b, kind))
+        # each kept id's term is rounded to 2^-44 of the largest
+        assert m[b] == z[b].max() and abs(mass[b] - np.exp(z[b][got].astype(np.float64) - m[b]).sum()) < V * 2.0 ** -45 + 1e-12
+        assert got[x[b]]
+    print("[nuclei of chosen rows B=%d V=%d top-p %.2f] flagged %d" % (B, V, top_p, flagged), flush=True)
+    assert flagged <= 0.1 * B
+
 
 def _chain_flags(zt, zq, d_ref, n_ref, dev, ua, uf, ud, top_p, window):
     """Per sequence, how far the oracle's draft-and-accept chain (at T = 1) stays comparable when
