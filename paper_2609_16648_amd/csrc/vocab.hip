@@ -841,8 +841,35 @@ __device__ double nuc_reference(const float *__restrict__ row, const RowStat *__
   return ref;
 }
 
-// whether the row takes the queue, and the exponent from which its ids are queued
-__device__ __forceinline__ bool nuc_peaked(double S) { return S >= 0.5 && S <= kNucFlat; }
+// The mass of the row's floor, what it would hold without its likely ids: the least mass of a
+// chunk times their number (the last chunk, which may be short, left out).  Holds barriers.
+__device__ double nuc_floor(const RowStat *__restrict__ st, int nch, double m, double *red_s) {
+  double least = INFINITY;
+  for (int c = threadIdx.x; c + 1 < nch; c += kNucThreads) least = fmin(least, st[c].sum * exp((double)st[c].max - m));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) least = fmin(least, __shfl_xor(least, o, kWave));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red_s[threadIdx.x >> 6] = least;
+  __syncthreads();
+  for (int w = 0; w < kNucThreads / 64; ++w) least = fmin(least, red_s[w]);
+  return least * nch;
+}
+
+// Whether the row takes the queue (and, past it, the bands), the same in every block that asks.  Past
+// kNucSureTopP the boundary of a row whose floor holds 1 - top_p lies so deep in it that queue and bands
+// only add to the histograms' work: there the floor is looked at first, where enough chunks show it.
+// (Accepts of 64 x 4 rows of 151936 ids, us, histograms alone / queue and bands / here: floor of 3%, top-p
+// 0.99 271 / 290 / 257, 0.999 271 / 303 / 258; floor of 0.02%, 0.99 258 / 198 / 199.  At 0.97 the look costs
+// launches of few rows more than it saves: 80 rows 180 / 179 / 188.)
+constexpr double kNucSureTopP = 0.98;
+constexpr int kNucFloorChunks = 4;
+__device__ __forceinline__ bool nuc_peaked(const RowStat *__restrict__ st, int nch, double m, double S, double top_p,
+                                           double *red_s) {
+  if (!(S >= 0.5 && S <= kNucFlat)) return false;
+  if (top_p <= kNucSureTopP) return true;
+  return nch >= kNucFloorChunks && nuc_floor(st, nch, m, red_s) <= S * (1.0 - top_p);
+}
+// the exponent from which the ids of a peaked row are queued
 __device__ __forceinline__ double nuc_cut(double S, double top_p) {
   const double c = log(S * (1.0 - top_p) / kNucTail);
   return c > -32.0 ? c : -32.0;
@@ -922,7 +949,7 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_hist_kernel(int V, double
   const int lo = (int)(((long)V * sg / S) & ~3l), hi = sg + 1 == S ? V : (int)(((long)V * (sg + 1) / S) & ~3l);
   const bool vec = (V & 3) == 0 && (row_stride & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
   unsigned long long *dst = part + ((long)r * S + sg) * kNucBins;
-  if (nuc_peaked(mass)) {
+  if (nuc_peaked(st + (long)r * nch, nch, m, mass, top_p, red_s)) {
     const double cut = nuc_cut(mass, top_p), guard = nuc_guard(mass, top_p, V);
     unsigned long long t = 0;
     nuc_visit(row + lo, hi - lo, vec, [&](float v, int x) {
@@ -1000,7 +1027,7 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
   double S_row;
   const double m = nuc_reference(row, st + (long)r * nch, nch, V, inv_td, red_m, red_a, red_s, S_row);
   const bool vec = (V & 3) == 0 && (row_stride & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
-  const bool peaked = nuc_peaked(S_row);
+  const bool peaked = nuc_peaked(st + (long)r * nch, nch, m, S_row, top_p, red_s);
   auto push = [&](float v, int x) {
     const unsigned slot = atomicAdd(&sh_qn, 1u);
     if (slot < (unsigned)kNucQueue) {
