@@ -25,8 +25,11 @@ struct DcaRow {          // per (cycle, position): what the gradient pass needs
   int g_rest, pad;
 };
 constexpr int kDcaIds = 4096;   // ids per block of the gradient pass
-// Gradients of this size and more are stored past the caches (1.9 GB: 2% off the launch); smaller
-// ones stay in the 256 MB last-level cache (62 MB: 48 us past it, 43 through it)
+// The gradient pass by the bytes of the gradient (as many logits are read):
+//  below the last-level cache        DCA_MEDIUM
+//  from that on                      DCA_STREAM  stored past the caches (1.9 GB: 2% off the launch;
+//                                                62 MB: 48 us past them, 43 through them)
+enum { DCA_MEDIUM, DCA_STREAM };
 constexpr size_t kDcaStreamBytes = size_t(256) << 20;
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
@@ -105,61 +108,74 @@ __global__ __launch_bounds__(1024) void dca_cycle_kernel(int K, int V, int topk,
   }
 }
 
-// nch blocks of kDcaIds ids per row, neighbouring blocks on neighbouring ids.  A row past the first rejection has
-// coefficient 0: its gradient is written without reading its logits (a quarter of the rows
-// with accepted lengths uniform in 0..3).  All loads of a thread are issued before the first
-// exponential; large gradients are written past the caches.  1024 cycles x 3 x 151936 ids:
-// 583 us, against 767 with every row read, one load in flight per thread and ordinary stores.
-__global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch, bool stream, const float *__restrict__ z,
+// kDcaIds ids of one row per block.  All loads of a thread are issued before the first exponential, 16 bytes
+// each where every row is aligned to them (VEC), else one id each.
+//  nch blocks per row, neighbouring blocks on neighbouring ids.  A row past the first rejection has
+// coefficient 0: its gradient is written without reading its logits (a quarter of the rows with accepted
+// lengths uniform in 0..3).
+// Whole loss, us (cycles x positions x ids; row by row with one load in flight and ordinary stores -> here):
+// 64 x 3 x 151936 67.9 -> 64.0, 100 x 3 x 50257 58.9 -> 43.1, 500 x 3 x 50257 331 -> 186, 1024 x 3 x 151936 1072 -> 886.
+template <bool VEC, int MODE>
+__global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch, const float *__restrict__ z,
                                                        const DcaRow *__restrict__ rows,
                                                        const int32_t *__restrict__ rec_ids,
                                                        const uint8_t *__restrict__ flags, float *__restrict__ grad) {
-  const long r = blockIdx.x / (unsigned)nch;
-  const int lo = (int)(blockIdx.x % (unsigned)nch) * kDcaIds, hi = min(V, lo + kDcaIds);
+  const bool flat = gridDim.y == 1;
+  const long r = flat ? blockIdx.x / (unsigned)nch : blockIdx.x;
+  const int lo = (int)(flat ? blockIdx.x % (unsigned)nch : blockIdx.y) * kDcaIds, hi = min(V, lo + kDcaIds);
+  const float *zr = z + r * V;
+  float *gr = grad + r * V;
+  const bool want = rows[r].coef != 0.0;
+  // the record's ids in this range carry their own flags; read beside the row's logits
+  int own_id = -1;
+  if (want && (int)threadIdx.x < topk) own_id = rec_ids[r * topk + threadIdx.x];
+  constexpr int kVec = kDcaIds / (4 * 256);
+  float v[kVec][4];
+#pragma unroll
+  for (int u = 0; u < kVec; ++u) {
+    if constexpr (VEC) {
+      const int x = lo + 4 * ((int)threadIdx.x + 256 * u);
+      const floatx4_t f = want && x < hi ? *reinterpret_cast<const floatx4_t *>(zr + x) : floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[u][q] = f[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int x = lo + (int)threadIdx.x + 256 * (4 * u + q);
+        v[u][q] = want && x < hi ? zr[x] : 0.f;
+      }
+    }
+  }
   const DcaRow d = rows[r];
   const float coef = (float)d.coef, M = (float)d.M, inv_s = (float)d.inv_s;
   const float rest = (float)((double)d.g_rest - d.gbar);
-  const float *zr = z + r * V;
-  float *gr = grad + r * V;
-  const bool vec = (V & 3) == 0 && ((reinterpret_cast<uintptr_t>(z) | reinterpret_cast<uintptr_t>(grad)) & 15) == 0;
   const bool zero = d.coef == 0.0;
-  // the record's ids in this range carry their own flags; read beside the row's logits
-  int own_id = -1;
-  if (!zero && (int)threadIdx.x < topk) own_id = rec_ids[r * topk + threadIdx.x];
+  if (zero || own_id < lo || own_id >= hi) own_id = -1;
   float own_z = 0.f;
   int own_flag = 0;
-  auto load_own = [&]() {
-    if (own_id < lo || own_id >= hi) own_id = -1;
-    if (own_id >= 0) {
-      own_z = zr[own_id];
-      own_flag = flags[r * topk + threadIdx.x];
-    }
-  };
-  if (vec) {
-    constexpr int kVec = kDcaIds / (4 * 256);
-    floatx4_t v[kVec];
+  if (own_id >= 0) {
+    own_z = zr[own_id];
+    own_flag = flags[r * topk + threadIdx.x];
+  }
 #pragma unroll
-    for (int u = 0; u < kVec; ++u) {
-      const int x = lo + 4 * ((int)threadIdx.x + 256 * u);
-      v[u] = !zero && x < hi ? *reinterpret_cast<const floatx4_t *>(zr + x) : floatx4_t{0.f, 0.f, 0.f, 0.f};
-    }
-    load_own();
+  for (int u = 0; u < kVec; ++u) {
+    floatx4_t o = {0.f, 0.f, 0.f, 0.f};
+    if (!zero) {
 #pragma unroll
-    for (int u = 0; u < kVec; ++u) {
+      for (int q = 0; q < 4; ++q) o[q] = coef * (expf(v[u][q] - M) * inv_s) * rest;
+    }
+    if constexpr (VEC) {
       const int x = lo + 4 * ((int)threadIdx.x + 256 * u);
       if (x >= hi) continue;
-      floatx4_t o = {0.f, 0.f, 0.f, 0.f};
-      if (!zero) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = coef * (expf(v[u][q] - M) * inv_s) * rest;
-      }
-      if (stream) __builtin_nontemporal_store(o, reinterpret_cast<floatx4_t *>(gr + x));
+      if (MODE == DCA_STREAM) __builtin_nontemporal_store(o, reinterpret_cast<floatx4_t *>(gr + x));
       else *reinterpret_cast<floatx4_t *>(gr + x) = o;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int x = lo + (int)threadIdx.x + 256 * (4 * u + q);
+        if (x < hi) gr[x] = o[q];
+      }
     }
-  } else {
-    load_own();
-    for (int x = lo + (int)threadIdx.x; x < hi; x += blockDim.x)
-      gr[x] = zero ? 0.f : coef * (expf(zr[x] - M) * inv_s) * rest;
   }
   // written over the rest's once the stores above are done
   if (!__syncthreads_or(own_id >= 0)) return;
@@ -193,8 +209,17 @@ void run_dca_loss(int N, int K, int V, int topk, const float *head_logits, const
   if (grad) {
     TraceScope ts("dca_grad", s);
     const int nch = (V + kDcaIds - 1) / kDcaIds;
-    hipLaunchKernelGGL(dca_grad_kernel, dim3((unsigned)N * K * nch), dim3(256), 0, s, V, topk, nch,
-                       (size_t)N * K * V * sizeof(float) >= kDcaStreamBytes, head_logits, rows, rec_ids, flags, grad);
+    const size_t bytes = (size_t)N * K * V * sizeof(float);
+    const int mode = bytes < kDcaStreamBytes ? DCA_MEDIUM : DCA_STREAM;
+    const bool vec = (V & 3) == 0 && (((uintptr_t)head_logits | (uintptr_t)grad) & 15) == 0;
+    // (a grid's dimension holds less than 2^32 threads)
+    const bool flat = (size_t)N * K * nch < (size_t(1) << 24) || nch == 1;
+    const dim3 grid = flat ? dim3((unsigned)N * K * nch) : dim3(N * K, nch);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, V, topk, nch, head_logits, rows, rec_ids, flags, grad);
+    };
+    if (mode == DCA_MEDIUM) launch(vec ? dca_grad_kernel<true, DCA_MEDIUM> : dca_grad_kernel<false, DCA_MEDIUM>);
+    else launch(vec ? dca_grad_kernel<true, DCA_STREAM> : dca_grad_kernel<false, DCA_STREAM>);
   }
 }
 

@@ -56,6 +56,37 @@ def test_dca_matches_oracle(N, K, V, topk, vgm):
             assert (grad[b, min(int(n[b]) + 1, K):] == 0).all()
 
 
+@pytest.mark.parametrize("N,K,V,off", [(9, 2, 50257, 0), (6, 3, 8196, 1), (5, 1, 4099, 3), (16, 3, 30000, 2),
+                                       (40, 5, 50257, 0), (41, 5, 50256, 0), (41, 5, 50256, 1),                 # below
+                                       (700, 2, 50257, 0), (1400, 1, 50256, 0), (1400, 1, 50256, 3)])           # above
+def test_dca_gradient_paths(N, K, V, off):
+    # gradients below 256 MB and above, rows on 16-byte boundaries and off them (an odd vocabulary,
+    # buffers `off` floats past one); NaN in the logits past the first rejection stays out of the gradient
+    need_gpu()
+    g = torch.Generator(device="cuda").manual_seed(N + V + off)
+    buf = lambda: torch.empty(N * K * V + 4, device="cuda")[off:off + N * K * V].view(N, K, V)
+    z, grad = buf(), buf()
+    z.normal_(generator=g).mul_(2.0)
+    ids = torch.rand((N, K, V), device="cuda", generator=g).topk(16, -1).indices.to(torch.int32).contiguous()
+    lp = torch.log_softmax(torch.rand((N, K, 17), device="cuda", generator=g) * 4.0, -1)[..., :16].contiguous()
+    lp = lp.to(torch.bfloat16)
+    n = torch.randint(0, K + 1, (N,), generator=g, device="cuda", dtype=torch.int32)
+    past = torch.arange(K, device="cuda")[None, :] > n[:, None]
+    some = np.unique(np.r_[0:8, N // 2:N // 2 + 8, max(N - 8, 0):N] % N)
+    zs, ids_s, lp_s, n_s = (t[torch.from_numpy(some).cuda()].cpu() for t in (z, ids, lp.float(), n))
+    z[past] = float("nan")
+    grad.fill_(7.0)
+    loss = torch.zeros(N, dtype=torch.float32, device="cuda")
+    alpha = torch.zeros((N, K), dtype=torch.float32, device="cuda")
+    gm.dca_loss(z, lp, ids, n, loss, alpha, grad, gm.Workspace(), vgm=True)
+    torch.cuda.synchronize()
+    assert (grad[past] == 0).all() and torch.isfinite(grad).all()
+    rl, _, rg = oracle.dca_loss(zs.numpy(), ids_s.numpy(), lp_s.numpy().astype(np.float64), n_s.numpy(), True)
+    np.testing.assert_allclose(loss.cpu().numpy()[some], rl, rtol=1e-6, atol=1e-7)
+    got = grad[torch.from_numpy(some).cuda()].cpu().numpy()
+    assert np.abs(got - rg).max() < 1e-5 * np.abs(rg).max()
+
+
 def test_dca_without_gradient_and_on_the_accepts_own_record():
     # the record taken by gm_spec_accept feeds the loss directly
     need_gpu()
