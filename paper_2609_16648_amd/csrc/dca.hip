@@ -26,11 +26,12 @@ struct DcaRow {          // per (cycle, position): what the gradient pass needs
 };
 constexpr int kDcaIds = 4096;   // ids per block of the gradient pass
 // The gradient pass by the bytes of the gradient (as many logits are read):
+//  up to the XCDs' L2s (8 x 4 MB)    DCA_SMALL   the row statistics have just brought the logits there
 //  below the last-level cache        DCA_MEDIUM
 //  from that on                      DCA_STREAM  stored past the caches (1.9 GB: 2% off the launch;
 //                                                62 MB: 48 us past them, 43 through them)
-enum { DCA_MEDIUM, DCA_STREAM };
-constexpr size_t kDcaStreamBytes = size_t(256) << 20;
+enum { DCA_SMALL, DCA_MEDIUM, DCA_STREAM };
+constexpr size_t kDcaSmallBytes = size_t(32) << 20, kDcaStreamBytes = size_t(256) << 20;
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -110,11 +111,15 @@ __global__ __launch_bounds__(1024) void dca_cycle_kernel(int K, int V, int topk,
 
 // kDcaIds ids of one row per block.  All loads of a thread are issued before the first exponential, 16 bytes
 // each where every row is aligned to them (VEC), else one id each.
-//  nch blocks per row, neighbouring blocks on neighbouring ids.  A row past the first rejection has
-// coefficient 0: its gradient is written without reading its logits (a quarter of the rows with accepted
-// lengths uniform in 0..3).
+//  DCA_MEDIUM, DCA_STREAM: nch blocks per row, neighbouring blocks on neighbouring ids.  A row past the first
+// rejection has coefficient 0: its gradient is written without reading its logits (a quarter of the rows
+// with accepted lengths uniform in 0..3).
+//  DCA_SMALL: the logits of every row are loaded at once, not behind the load of the row's coefficient, by a
+// grid of rows x nch, the row statistics' order: with rows a multiple of eight a row's logits are in the L2 of
+// the XCD that reads them.
 // Whole loss, us (cycles x positions x ids; row by row with one load in flight and ordinary stores -> here):
-// 64 x 3 x 151936 67.9 -> 64.0, 100 x 3 x 50257 58.9 -> 43.1, 500 x 3 x 50257 331 -> 186, 1024 x 3 x 151936 1072 -> 886.
+// 8 x 3 x 151936 19.0 -> 19.4 (DCA_MEDIUM 21.4), 12 x 5 x 128256 30.6 -> 30.5 (32.5), 64 x 3 x 151936 67.9 -> 64.0
+// (DCA_SMALL 68.1), 100 x 3 x 50257 58.9 -> 43.1 (45.7), 500 x 3 x 50257 331 -> 186, 1024 x 3 x 151936 1072 -> 886.
 template <bool VEC, int MODE>
 __global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch, const float *__restrict__ z,
                                                        const DcaRow *__restrict__ rows,
@@ -125,7 +130,7 @@ __global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch,
   const int lo = (int)(flat ? blockIdx.x % (unsigned)nch : blockIdx.y) * kDcaIds, hi = min(V, lo + kDcaIds);
   const float *zr = z + r * V;
   float *gr = grad + r * V;
-  const bool want = rows[r].coef != 0.0;
+  const bool want = MODE == DCA_SMALL || rows[r].coef != 0.0;
   // the record's ids in this range carry their own flags; read beside the row's logits
   int own_id = -1;
   if (want && (int)threadIdx.x < topk) own_id = rec_ids[r * topk + threadIdx.x];
@@ -210,15 +215,16 @@ void run_dca_loss(int N, int K, int V, int topk, const float *head_logits, const
     TraceScope ts("dca_grad", s);
     const int nch = (V + kDcaIds - 1) / kDcaIds;
     const size_t bytes = (size_t)N * K * V * sizeof(float);
-    const int mode = bytes < kDcaStreamBytes ? DCA_MEDIUM : DCA_STREAM;
+    const int mode = bytes <= kDcaSmallBytes ? DCA_SMALL : bytes < kDcaStreamBytes ? DCA_MEDIUM : DCA_STREAM;
     const bool vec = (V & 3) == 0 && (((uintptr_t)head_logits | (uintptr_t)grad) & 15) == 0;
     // (a grid's dimension holds less than 2^32 threads)
-    const bool flat = (size_t)N * K * nch < (size_t(1) << 24) || nch == 1;
+    const bool flat = nch == 1 || (mode != DCA_SMALL && (size_t)N * K * nch < (size_t(1) << 24));
     const dim3 grid = flat ? dim3((unsigned)N * K * nch) : dim3(N * K, nch);
     auto launch = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, V, topk, nch, head_logits, rows, rec_ids, flags, grad);
     };
-    if (mode == DCA_MEDIUM) launch(vec ? dca_grad_kernel<true, DCA_MEDIUM> : dca_grad_kernel<false, DCA_MEDIUM>);
+    if (mode == DCA_SMALL) launch(vec ? dca_grad_kernel<true, DCA_SMALL> : dca_grad_kernel<false, DCA_SMALL>);
+    else if (mode == DCA_MEDIUM) launch(vec ? dca_grad_kernel<true, DCA_MEDIUM> : dca_grad_kernel<false, DCA_MEDIUM>);
     else launch(vec ? dca_grad_kernel<true, DCA_STREAM> : dca_grad_kernel<false, DCA_STREAM>);
   }
 }

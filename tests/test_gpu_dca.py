@@ -56,11 +56,11 @@ def test_dca_matches_oracle(N, K, V, topk, vgm):
             assert (grad[b, min(int(n[b]) + 1, K):] == 0).all()
 
 
-@pytest.mark.parametrize("N,K,V,off", [(9, 2, 50257, 0), (6, 3, 8196, 1), (5, 1, 4099, 3), (16, 3, 30000, 2),
-                                       (40, 5, 50257, 0), (41, 5, 50256, 0), (41, 5, 50256, 1),                 # below
-                                       (700, 2, 50257, 0), (1400, 1, 50256, 0), (1400, 1, 50256, 3)])           # above
+@pytest.mark.parametrize("N,K,V,off", [(9, 2, 50257, 0), (6, 3, 8196, 1), (5, 1, 4099, 3), (16, 3, 30000, 2),   # small
+                                       (40, 5, 50257, 0), (41, 5, 50256, 0), (41, 5, 50256, 1),                 # medium
+                                       (700, 2, 50257, 0), (1400, 1, 50256, 0), (1400, 1, 50256, 3)])           # large
 def test_dca_gradient_paths(N, K, V, off):
-    # gradients below 256 MB and above, rows on 16-byte boundaries and off them (an odd vocabulary,
+    # gradients up to 32 MB, below 256 MB and above, rows on 16-byte boundaries and off them (an odd vocabulary,
     # buffers `off` floats past one); NaN in the logits past the first rejection stays out of the gradient
     need_gpu()
     g = torch.Generator(device="cuda").manual_seed(N + V + off)
