@@ -132,16 +132,16 @@ extern "C" size_t gm_workspace_size(int op, const gm_model_config *cfg, int B, i
       return plan_accept(B, k, cfg->vocab).total;
     case GM_OP_VERIFY_FORWARD:
       if (check_config(cfg, B, k) != GM_OK) return 0;
-      return plan_forward(*cfg, B, k, max_ctx).total;
+      return plan_forward(*cfg, B, k).total;
     case GM_OP_VERIFY_ATTENTION:
       if (check_config(cfg, B, k) != GM_OK) return 0;
-      return plan_attention(*cfg, B, k + 1, max_ctx).total;
+      return plan_attention(*cfg, B, k + 1).total;
     case GM_OP_MTP_DRAFT:
       if (check_config(cfg, B, k) != GM_OK) return 0;
-      return plan_mtp(*cfg, B, k, max_ctx).total;
+      return plan_mtp(*cfg, B, k).total;
     case GM_OP_MTP_RECONSTRUCT:
       if (k < 1 || check_config(cfg, B, k) != GM_OK) return 0;
-      return plan_mtp(*cfg, B, k, max_ctx).total;
+      return plan_mtp(*cfg, B, k).total;
     case GM_OP_DCA_LOSS:
       if (!cfg || k < 1 || cfg->vocab < 1 || cfg->vocab > kMaxVocab) return 0;
       return dca_workspace(B, k, cfg->vocab);
@@ -309,7 +309,7 @@ extern "C" gm_status gm_verify_attention(const gm_model_config *cfg, const gm_kv
   if (st != GM_OK) return st;
   if (B == 0) return GM_OK;
   if (!q || !out) return fail(GM_ERR_INVALID_ARG, "null q / out");
-  const AttnPlan p = plan_attention(*cfg, B, k + 1, cache->max_ctx);
+  const AttnPlan p = plan_attention(*cfg, B, k + 1);
   st = check_ws(ws, ws_bytes, p.total);
   if (st != GM_OK) return st;
   AttnArgs a = attn_args(*cfg, *cache, layer, B, k + 1, cache->seq_lens, 0, nullptr);
@@ -337,7 +337,7 @@ extern "C" gm_status gm_verify_forward(const gm_model_config *cfg, const gm_mode
   if (B == 0) return GM_OK;
   if (!tokens || !logits || !hidden) return fail(GM_ERR_INVALID_ARG, "null tokens / logits / hidden");
   if (target_stats && !(temperature > 0.f)) return fail(GM_ERR_INVALID_ARG, "target_stats need a temperature > 0");
-  const ForwardPlan p = plan_forward(*cfg, B, k, cache->max_ctx);
+  const ForwardPlan p = plan_forward(*cfg, B, k);
   st = check_ws(ws, ws_bytes, p.total);
   if (st != GM_OK) return st;
   run_verify_forward(*cfg, *w, *cache, B, k, tokens, logits, hidden, target_stats ? 1.0f / temperature : 1.0f,
@@ -370,7 +370,7 @@ extern "C" gm_status gm_mtp_draft(const gm_model_config *cfg, const gm_mtp_weigh
   if (!verify_hidden || !n_accept || !out_tokens || !drafts || !draft_logits)
     return fail(GM_ERR_INVALID_ARG, "null MTP input / output");
   if (mode == GM_SAMPLE && !u_draft) return fail(GM_ERR_INVALID_ARG, "sample mode needs u_draft");
-  const MtpPlan p = plan_mtp(*cfg, B, k, mtp_cache->max_ctx);
+  const MtpPlan p = plan_mtp(*cfg, B, k);
   st = check_ws(ws, ws_bytes, p.total);
   if (st != GM_OK) return st;
   run_mtp_draft(*cfg, *mtp, *shared, *mtp_cache, B, k, mode, 1.0f / temperature,
@@ -398,7 +398,7 @@ extern "C" gm_status gm_mtp_reconstruct(const gm_model_config *cfg, const gm_mtp
   if (R == 0) return GM_OK;
   if (!start_hidden || !start_tokens || !head_logits || (K > 1 && !drafts))
     return fail(GM_ERR_INVALID_ARG, "null reconstruction input / output");
-  const MtpPlan p = plan_mtp(*cfg, R, K, mtp_cache->max_ctx);
+  const MtpPlan p = plan_mtp(*cfg, R, K);
   st = check_ws(ws, ws_bytes, p.total);
   if (st != GM_OK) return st;
   run_mtp_reconstruct(*cfg, *mtp, *shared, *mtp_cache, R, K, start_hidden, start_tokens, drafts, head_logits, p,

@@ -27,7 +27,6 @@
 //    online softmax (exp2 domain) rescales only when a running max grows by
 //    more than 2^kLazyLog2, so most tiles need no rescale.
 // float32 path: a workgroup per (row, head), its four waves splitting the tokens.
-#include <algorithm>
 #include <atomic>
 
 #include "common.h"
@@ -732,7 +731,7 @@ int resident_groups(int block) {
 }
 }  // namespace
 
-AttnPlan plan_attention(const gm_model_config &cfg, int B, int R, int max_ctx) {
+AttnPlan plan_attention(const gm_model_config &cfg, int B, int R) {
   AttnPlan p{};
   const int G = cfg.n_heads / cfg.n_kv_heads;
   const int rows = G * R;
@@ -747,12 +746,9 @@ AttnPlan plan_attention(const gm_model_config &cfg, int B, int R, int max_ctx) {
   // 32 sequences of 16-32K tokens: 500 us with one round, 530 with two, 577 with four).
   if (parts < 1) parts = 1;
   p.parts = (int)parts;
-  // The kernels use parts + B slots.  The size that callers are told has a slot per 4096 tokens of the
-  // context bound as well, so that gm_workspace_size keeps its values: the slots past parts + B are unused.
-  const long tiles_max = (long)B * (((long)max_ctx + R + 15) / 16);
-  const long slots = std::max(parts, (tiles_max + 4096 / 16 - 1) / (4096 / 16));
+  // the partial of (range p, sequence b) is in slot p + b
   Carve c;
-  const size_t n = (size_t)(slots + B) * cfg.n_kv_heads * p.rows_pad;
+  const size_t n = (size_t)(parts + B) * cfg.n_kv_heads * p.rows_pad;
   p.part_o = c.take(n * 128 * sizeof(float));
   p.part_ml = c.take(n * sizeof(float2));
   p.cum = c.take((size_t)(B + 1) * sizeof(int32_t));

@@ -74,7 +74,7 @@ RopeArgs rope_args(const gm_model_config &cfg, const gm_kv_cache &c, int layer, 
 }  // namespace
 
 // ---------------------------------------------------------------- verify forward
-ForwardPlan plan_forward(const gm_model_config &cfg, int B, int k, int max_ctx) {
+ForwardPlan plan_forward(const gm_model_config &cfg, int B, int k) {
   ForwardPlan p{};
   const size_t M = (size_t)B * (k + 1), e = esize(cfg.dtype);
   const size_t qd = (size_t)cfg.n_heads * cfg.head_dim;
@@ -84,7 +84,7 @@ ForwardPlan plan_forward(const gm_model_config &cfg, int B, int k, int max_ctx) 
   p.qkv = c.take(M * qkv_width(cfg) * sizeof(float));
   p.q = c.take(M * qd * e);
   p.attn = c.take(M * qd * e);
-  p.attn_plan = plan_attention(cfg, B, k + 1, max_ctx);
+  p.attn_plan = plan_attention(cfg, B, k + 1);
   p.attn_ws = c.take(p.attn_plan.total);
   p.part = c.take(part_bytes(cfg, (int)M, false));
   // the LM head's tile statistics when the caller wants the rows' softmax statistics
@@ -138,7 +138,7 @@ void run_verify_forward(const gm_model_config &cfg, const gm_model_weights &w, c
 }
 
 // ---------------------------------------------------------------- MTP draft
-MtpPlan plan_mtp(const gm_model_config &cfg, int B, int k, int max_ctx) {
+MtpPlan plan_mtp(const gm_model_config &cfg, int B, int k) {
   MtpPlan p{};
   const size_t R = k + 1, Me = (size_t)B * R, e = esize(cfg.dtype), H = cfg.hidden;
   const size_t qd = (size_t)cfg.n_heads * cfg.head_dim;
@@ -152,8 +152,8 @@ MtpPlan plan_mtp(const gm_model_config &cfg, int B, int k, int max_ctx) {
   p.q = c.take(Me * qd * e);
   p.attn = c.take(Me * qd * e);
   p.attn_g = c.take((size_t)B * qd * e);
-  p.attn_ext = plan_attention(cfg, B, (int)R, max_ctx);
-  p.attn_chain = plan_attention(cfg, B, 1, max_ctx + 2 * k);
+  p.attn_ext = plan_attention(cfg, B, (int)R);
+  p.attn_chain = plan_attention(cfg, B, 1);
   p.attn_ws = c.take(p.attn_ext.total > p.attn_chain.total ? p.attn_ext.total : p.attn_chain.total);
   const int V = cfg.vocab;
   p.stat = c.take(sizeof(RowStat) * (size_t)B * plan_lm_head(cfg.dtype, B, V, cfg.hidden).tiles);

@@ -25,7 +25,7 @@ struct AttnPlan {
   int rows_pad;        // 16-row tiles * 16
   size_t part_o, part_ml, cum, total;
 };
-AttnPlan plan_attention(const gm_model_config &cfg, int B, int R, int max_ctx);
+AttnPlan plan_attention(const gm_model_config &cfg, int B, int R);
 
 struct AttnArgs {
   int dtype, B, R, n_heads, n_kv, head_dim;
@@ -138,7 +138,7 @@ struct ForwardPlan {
   size_t nbuf, act, qkv, q, attn, attn_ws, part, tiles, total;
   AttnPlan attn_plan;
 };
-ForwardPlan plan_forward(const gm_model_config &cfg, int B, int k, int max_ctx);
+ForwardPlan plan_forward(const gm_model_config &cfg, int B, int k);
 // target_stats (may be null): one RowStat per logits row at 1 / inv_t, from the LM head's epilogue
 void run_verify_forward(const gm_model_config &cfg, const gm_model_weights &w, const gm_kv_cache &c, int B, int k,
                         const int32_t *tokens, float *logits, float *hidden, float inv_t, RowStat *target_stats,
@@ -148,8 +148,8 @@ struct MtpPlan {
   size_t u, x, xg, nbuf, act, qkv, q, attn, attn_g, attn_ws, stat, nuc, sel, wsum, psum, nucpart, part, total;
   AttnPlan attn_ext, attn_chain;
 };
-MtpPlan plan_mtp(const gm_model_config &cfg, int B, int k, int max_ctx);
-// draft-path reconstruction of R recorded cycles over K depths (workspace: plan_mtp(cfg, R, K, max_ctx))
+MtpPlan plan_mtp(const gm_model_config &cfg, int B, int k);
+// draft-path reconstruction of R recorded cycles over K depths (workspace: plan_mtp(cfg, R, K))
 void run_mtp_reconstruct(const gm_model_config &cfg, const gm_mtp_weights &mtp, const gm_model_weights &shared,
                          const gm_kv_cache &c, int R, int K, const float *start_hidden, const int32_t *start_tokens,
                          const int32_t *drafts, float *head_logits, const MtpPlan &p, char *ws, int32_t *dev_err,

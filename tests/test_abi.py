@@ -43,10 +43,12 @@ def test_workspace_sizes():
     assert gm.workspace_size(gm.GM_OP_VERIFY_FORWARD, cfg, 64, 16, 4096) == 0      # k beyond the limit
     bad = _cfg(synth.ModelShape(1, 256, 4, 4, 64, 1024, 1024, dtype="bf16"))       # bf16 needs head_dim 128
     assert gm.workspace_size(gm.GM_OP_VERIFY_FORWARD, bad, 4, 3, 128) == 0
-    # the attention partials grow with the context bound
-    a = gm.workspace_size(gm.GM_OP_VERIFY_ATTENTION, cfg, 32, 7, 32768)
-    b = gm.workspace_size(gm.GM_OP_VERIFY_ATTENTION, cfg, 32, 7, 1024)
-    assert a > b
+    # the attention's partials: one slot per resident workgroup and sequence, whatever the context bound
+    size = lambda B, ctx: gm.workspace_size(gm.GM_OP_VERIFY_ATTENTION, cfg, B, 7, ctx)
+    assert size(32, 1024) <= size(32, 32768) <= size(32, 1 << 20)
+    assert size(64, 1024) > size(32, 1024)
+    slot = 8 * 32 * (128 * 4 + 8)                # 8 KV heads x 32 rows of 128 floats, a maximum and a sum each
+    assert size(128, 32768) <= (256 + 128) * slot + (1 << 12)    # a workgroup per CU
 
 
 def test_spec_accept_rejects_bad_arguments():

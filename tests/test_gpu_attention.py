@@ -132,6 +132,30 @@ def test_bf16_attention_tiles_per_range(tiles):
         assert _row_err(got, oracle.attention(q, k, v, vis)) < LONG_TOL
 
 
+class _Guarded(gm.Workspace):
+    """Hands out exactly the bytes that are asked for, in front of a guard."""
+    GUARD = 1 << 20
+
+    def get(self, nbytes):
+        self.n = nbytes
+        self.buf = torch.full((nbytes + self.GUARD,), 0xA5, dtype=torch.uint8, device="cuda")
+        return self.buf[:nbytes]
+
+
+@pytest.mark.parametrize("lens,k", [([9000] * 3, 7), ([700] * 150, 3), ([40] * 600, 0), ([30000], 1)])
+def test_bf16_attention_stays_in_its_workspace(lens, k):
+    # sequences at the context bound, cut over as many ranges as there are: nothing past the reported size
+    need_gpu()
+    shape, lens = synth.QWEN3_4B_LAYER, np.array(lens)
+    cache = gm.PagedCache(shape, 1, lens, lens + k + 1, page_size=16, seed=1)
+    q = torch.randn((len(lens), k + 1, shape.n_heads, 128), device="cuda").to(torch.bfloat16)
+    ws, out = _Guarded(), torch.empty_like(q)
+    gm.verify_attention(gm.model_config(shape), cache, 0, q, out, ws)
+    torch.cuda.synchronize()
+    assert (ws.buf[ws.n:] == 0xA5).all() and (ws.buf[:ws.n] != 0xA5).any()
+    assert (out == 0).all()                      # zero values, whatever the weights
+
+
 def test_f32_attention_matches_oracle():
     need_gpu()
     shape = synth.TINY
