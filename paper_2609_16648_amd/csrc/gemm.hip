@@ -560,9 +560,12 @@ void launch_f32(const GemmF &g, hipStream_t s) {
 // two row tiles: the products and the fragment reads for padding rows were not hidden
 // by the weight stream (7 rows: 126 us per launch with four row tiles, 117 with one).
 constexpr int kLmStrips = 10;
-// Outputs from this width (two columns of 128 per CU) are wide enough to give every wave strips
-// of its own; narrower ones are split along K by the tiled kernel.
-constexpr int kLmStripsMinN = 256 * 128;
+// Logits without statistics take the strip ranges from seven strips for each of 1024 waves on: a range's
+// loop loads nine whatever it holds, and narrower outputs give the tiled kernel enough columns, or K splits
+// of them.  (Verify layer with LM head, K 2560, us, tiled -> ranges at 4 and 64 rows: vocabulary 32000 95 -> 127
+// and 112 -> 158, 33664 108 -> 127 and 130 -> 158, 65536 121 -> 136 and 143 -> 166, 98304 144 -> 148 and 177 -> 177,
+// 128256 177 -> 166 and 225 -> 192; K 4096, 65536 172 -> 177 and 202 -> 216.)
+constexpr int kLmStripsMinN = 7 * 16 * 1024;
 // Two slots: one k-step (10 KiB of weights per wave) in flight while the other is consumed.
 // With four waves per CU that is about as much as the HBM queues serve best; deeper rings put
 // more in flight and were slower (measured at 64 rows: 2 slots 146 us per launch, 4 slots

@@ -355,13 +355,17 @@ def test_strip_ranges_with_idle_waves():
     _check_stats("strip ranges, 10248 strips", stats, logits, 1.0)
 
 
-@pytest.mark.parametrize("B,k", [(1, 0), (16, 0), (17, 0), (8, 3), (11, 2), (16, 3), (13, 4)])
-def test_lm_head_rows_by_kernel(B, k):
+@pytest.mark.parametrize("B,k,vocab", [(B, k, 128 * 263) for B, k in
+                                       [(1, 0), (16, 0), (17, 0), (8, 3), (11, 2), (16, 3), (13, 4)]] +
+                         # logits without statistics: the last vocabulary of the tiled kernel, the first and
+                         # an odd one of the strip ranges
+                         [(5, 1, 128 * 895), (1, 0, 128 * 896), (17, 0, 128 * 896), (16, 3, 128 * 901), (13, 4, 128 * 901)])
+def test_lm_head_rows_by_kernel(B, k, vocab):
     # 1, 16, 17, 32, 33, 64 and 65 rows: the edges of the strip-range kernel's row tiles and of its
     # range, on a vocabulary that leaves the last waves short ranges; the statistics of the same rows
     # agree with the logits
     need_gpu()
-    shape = dataclasses.replace(synth.QWEN3_4B_LAYER, hidden=256, n_heads=4, n_kv_heads=2, ffn=512, vocab=128 * 263)
+    shape = dataclasses.replace(synth.QWEN3_4B_LAYER, hidden=256, n_heads=4, n_kv_heads=2, ffn=512, vocab=vocab)
     W = synth.model_weights(shape)
     lens = 5 + 3 * np.arange(B)
     caches = synth_caches(shape, lens, 1)
