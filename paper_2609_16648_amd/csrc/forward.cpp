@@ -33,7 +33,7 @@ PendingNorm gemm_norm(const char *name, int dt, int epi, int M, int N, int K, co
                       float *Y, float *part, const void *norm_w, float eps, void *nbuf, hipStream_t s) {
   const int sp = launch_gemm(name, dt, epi, M, N, K, X, ldx, W, Y, N, part, s, nullptr, 1.f, true);
   if (dt != GM_BF16) return PendingNorm{Y, norm_w, eps};
-  if (sp > 1) launch_reduce_norm(dt, epi, M, N, sp, part, Y, norm_w, eps, nbuf, s);
+  if (sp > 1) launch_reduce_norm(epi, M, N, sp, part, Y, norm_w, eps, nbuf, s);
   else launch_rmsnorm(dt, M, N, eps, Y, norm_w, nbuf, s);
   return PendingNorm{};
 }

@@ -357,13 +357,13 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(GemmS g) {
 
 // The K-split partials of a [M][N] float32 output summed in split order (plus the
 // residual already in Y for EPI_ADD_F32) into Y, followed by the RMSNorm of each
-// row into `out` (model dtype, weight w): the reduce and the norm that always
+// row into `out` (bf16, weight w): the reduce and the norm that always
 // follows it in one pass.  One block per row, a float4 column group per thread
 // and step (N % 4 == 0), the row kept in LDS between the two passes.
-template <typename T, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(1024) void reduce_norm_kernel(int M, int N, int splits, const float *__restrict__ part,
-                                                           float *__restrict__ Y, const T *__restrict__ w, float eps,
-                                                           T *__restrict__ out) {
+                                                           float *__restrict__ Y, const bf16 *__restrict__ w, float eps,
+                                                           bf16 *__restrict__ out) {
   extern __shared__ float row_sh[];   // [N]
   __shared__ float red[16];
   const int m = blockIdx.x;
@@ -381,13 +381,13 @@ __global__ __launch_bounds__(1024) void reduce_norm_kernel(int M, int N, int spl
   }
   ss = block_sum(ss, red);
   const float inv = 1.0f / sqrtf(ss / (float)N + eps);
-  T *o = out + (long)m * N;
+  bf16 *o = out + (long)m * N;
   for (int n = threadIdx.x * 4; n < N; n += blockDim.x * 4) {
     const float4 a = *reinterpret_cast<const float4 *>(row_sh + n);
-    Elem<T>::store(o, n, a.x * inv * Elem<T>::load(w, n));
-    Elem<T>::store(o, n + 1, a.y * inv * Elem<T>::load(w, n + 1));
-    Elem<T>::store(o, n + 2, a.z * inv * Elem<T>::load(w, n + 2));
-    Elem<T>::store(o, n + 3, a.w * inv * Elem<T>::load(w, n + 3));
+    Elem<bf16>::store(o, n, a.x * inv * Elem<bf16>::load(w, n));
+    Elem<bf16>::store(o, n + 1, a.y * inv * Elem<bf16>::load(w, n + 1));
+    Elem<bf16>::store(o, n + 2, a.z * inv * Elem<bf16>::load(w, n + 2));
+    Elem<bf16>::store(o, n + 3, a.w * inv * Elem<bf16>::load(w, n + 3));
   }
 }
 
@@ -992,29 +992,20 @@ int launch_gemm(const char *name, int dtype, int epi, int M, int N, int K, const
   return 1;
 }
 
-void launch_reduce_norm(int dtype, int epi, int M, int N, int splits, const float *part, float *Y, const void *norm_w,
-                        float eps, void *out, hipStream_t s) {
+void launch_reduce_norm(int epi, int M, int N, int splits, const float *part, float *Y, const void *norm_w, float eps,
+                        void *out, hipStream_t s) {
   if (M <= 0) return;
   TraceScope ts("reduce_norm", s);
   int threads = ((N / 4 + 63) / 64) * 64;   // one float4 column group per thread when N <= 4096
   if (threads > 1024) threads = 1024;
   const dim3 grid(M), block(threads);
   const size_t lds = (size_t)N * sizeof(float);
-  if (dtype == GM_BF16) {
-    if (epi == EPI_ADD_F32)
-      hipLaunchKernelGGL((reduce_norm_kernel<bf16, EPI_ADD_F32>), grid, block, lds, s, M, N, splits, part, Y,
-                         (const bf16 *)norm_w, eps, (bf16 *)out);
-    else
-      hipLaunchKernelGGL((reduce_norm_kernel<bf16, EPI_STORE_F32>), grid, block, lds, s, M, N, splits, part, Y,
-                         (const bf16 *)norm_w, eps, (bf16 *)out);
-  } else {
-    if (epi == EPI_ADD_F32)
-      hipLaunchKernelGGL((reduce_norm_kernel<float, EPI_ADD_F32>), grid, block, lds, s, M, N, splits, part, Y,
-                         (const float *)norm_w, eps, (float *)out);
-    else
-      hipLaunchKernelGGL((reduce_norm_kernel<float, EPI_STORE_F32>), grid, block, lds, s, M, N, splits, part, Y,
-                         (const float *)norm_w, eps, (float *)out);
-  }
+  if (epi == EPI_ADD_F32)
+    hipLaunchKernelGGL(reduce_norm_kernel<EPI_ADD_F32>, grid, block, lds, s, M, N, splits, part, Y,
+                       (const bf16 *)norm_w, eps, (bf16 *)out);
+  else
+    hipLaunchKernelGGL(reduce_norm_kernel<EPI_STORE_F32>, grid, block, lds, s, M, N, splits, part, Y,
+                       (const bf16 *)norm_w, eps, (bf16 *)out);
 }
 
 }  // namespace gm
