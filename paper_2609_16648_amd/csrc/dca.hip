@@ -26,12 +26,16 @@ struct DcaRow {          // per (cycle, position): what the gradient pass needs
 };
 constexpr int kDcaIds = 4096;   // ids per block of the gradient pass
 // The gradient pass by the bytes of the gradient (as many logits are read):
-//  up to the XCDs' L2s (8 x 4 MB)    DCA_SMALL   the row statistics have just brought the logits there
+//  up to the XCDs' L2s (8 x 4 MB)    DCA_SMALL   the row statistics have just brought the logits there; without
+//                                                masking (no row can be left unread) and with rows a multiple
+//                                                of eight up to 128 MB (34 x 4 x 128256: 47.2 us, 48.9 DCA_MEDIUM;
+//                                                64 x 3 x 151936: 68.1 and 68.5; 140 x 3 x 151936: 156 and 153)
 //  below the last-level cache        DCA_MEDIUM
 //  from that on                      DCA_STREAM  stored past the caches (1.9 GB: 2% off the launch;
 //                                                62 MB: 48 us past them, 43 through them)
 enum { DCA_SMALL, DCA_MEDIUM, DCA_STREAM };
-constexpr size_t kDcaSmallBytes = size_t(32) << 20, kDcaStreamBytes = size_t(256) << 20;
+constexpr size_t kDcaSmallBytes = size_t(32) << 20, kDcaRowBytes = size_t(128) << 20;
+constexpr size_t kDcaStreamBytes = size_t(256) << 20;
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -215,7 +219,8 @@ void run_dca_loss(int N, int K, int V, int topk, const float *head_logits, const
     TraceScope ts("dca_grad", s);
     const int nch = (V + kDcaIds - 1) / kDcaIds;
     const size_t bytes = (size_t)N * K * V * sizeof(float);
-    const int mode = bytes <= kDcaSmallBytes ? DCA_SMALL : bytes < kDcaStreamBytes ? DCA_MEDIUM : DCA_STREAM;
+    const bool small = bytes <= kDcaSmallBytes || (!vgm && (long)N * K % 8 == 0 && bytes <= kDcaRowBytes);
+    const int mode = small ? DCA_SMALL : bytes < kDcaStreamBytes ? DCA_MEDIUM : DCA_STREAM;
     const bool vec = (V & 3) == 0 && (((uintptr_t)head_logits | (uintptr_t)grad) & 15) == 0;
     // (a grid's dimension holds less than 2^32 threads)
     const bool flat = nch == 1 || (mode != DCA_SMALL && (size_t)N * K * nch < (size_t(1) << 24));

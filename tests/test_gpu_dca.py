@@ -37,6 +37,7 @@ def _gpu(zq, ids, logp, n, vgm, with_grad=True):
 
 
 @pytest.mark.parametrize("N,K,V,topk,vgm", [(16, 3, 151936, 64, True), (16, 3, 151936, 64, False),
+                                            (24, 3, 151936, 32, False),   # unmasked, 72 rows, past the L2s
                                             (8, 7, 20000, 64, True), (33, 1, 1000, 16, True), (5, 2, 64, 64, True),
                                             # rows past one gradient block by one id (and off 16 bytes), by four
                                             (6, 4, 4097, 33, True), (6, 3, 8196, 64, True)])
