@@ -47,10 +47,11 @@ constexpr int kAttnRing = 3;            // K/V register buffers per wave
 constexpr float kLazyLog2 = 8.f;        // rescale threshold of the running max (log2 units)
 // Ranges of this many tiles store the partials of cut sequences through the caches, shorter and longer
 // ones past them (attention and combine, us, past the caches -> through them, by tiles per range:
-// 0.6: 18.4 -> 19.2 and 18.3 -> 20.1; 2.5: 22.1 -> 24.4 and 17.6 -> 19.8; 6.5: 21.4 -> 20.5; 10.5: 42.4 -> 38.1;
+// 0.6: 18.4 -> 19.2 and 18.3 -> 20.1; 2.5: 22.1 -> 24.4 and 17.6 -> 19.8; 3.9: 24.5 -> 25.9; 4.2: 20.1 -> 21.5;
+// 4.4: 27.3 -> 26.2; 5: 25.8 -> 23.9; 6.5: 21.4 -> 20.5; 10.5: 42.4 -> 38.1;
 // 16: 36.7 -> 35.5; 80: 120.9 -> 118.6; 94: 133.2 -> 131.9; 117: 168.2 -> 168.2; 384: 496.5 -> 499.9;
 // 576: 750 -> 775).
-constexpr int kPartCachedTiles = 4, kPartStreamTiles = 128;
+constexpr int kPartCachedTiles = 5, kPartStreamTiles = 128;
 
 struct AttnK {
   const uint16_t *kp, *vp;
