@@ -26,15 +26,14 @@ struct DcaRow {          // per (cycle, position): what the gradient pass needs
 };
 constexpr int kDcaIds = 4096;   // ids per block of the gradient pass
 // The gradient pass by the bytes of the gradient (as many logits are read):
-//  up to the XCDs' L2s (8 x 4 MB)    DCA_SMALL   the row statistics have just brought the logits there; without
-//                                                masking (no row can be left unread) and with rows a multiple
-//                                                of eight up to 128 MB (34 x 4 x 128256: 47.2 us, 48.9 DCA_MEDIUM;
-//                                                64 x 3 x 151936: 68.1 and 68.5; 140 x 3 x 151936: 156 and 153)
+//  up to the XCDs' L2s (8 x 4 MB)    DCA_SMALL   the row statistics have just brought the logits there
 //  below the last-level cache        DCA_MEDIUM
 //  from that on                      DCA_STREAM  stored past the caches (1.9 GB: 2% off the launch;
 //                                                62 MB: 48 us past them, 43 through them)
+// With rows a multiple of eight and without masking, where no row can be left unread, DCA_SMALL goes on to 96 MB
+// (34 x 4 x 128256, 70 MB: 47.3 us, 48.9 DCA_MEDIUM; 64 x 3 x 151936, 117 MB: 70.2 and 68.4).
 enum { DCA_SMALL, DCA_MEDIUM, DCA_STREAM };
-constexpr size_t kDcaSmallBytes = size_t(32) << 20, kDcaRowBytes = size_t(128) << 20;
+constexpr size_t kDcaSmallBytes = size_t(32) << 20, kDcaRowBytes = size_t(96) << 20;
 constexpr size_t kDcaStreamBytes = size_t(256) << 20;
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
@@ -113,17 +112,18 @@ __global__ __launch_bounds__(1024) void dca_cycle_kernel(int K, int V, int topk,
   }
 }
 
-// kDcaIds ids of one row per block.  All loads of a thread are issued before the first exponential, 16 bytes
-// each where every row is aligned to them (VEC), else one id each.
-//  DCA_MEDIUM, DCA_STREAM: nch blocks per row, neighbouring blocks on neighbouring ids.  A row past the first
-// rejection has coefficient 0: its gradient is written without reading its logits (a quarter of the rows
-// with accepted lengths uniform in 0..3).
-//  DCA_SMALL: the logits of every row are loaded at once, not behind the load of the row's coefficient, by a
-// grid of rows x nch, the row statistics' order: with rows a multiple of eight a row's logits are in the L2 of
-// the XCD that reads them.
-// Whole loss, us (cycles x positions x ids; row by row with one load in flight and ordinary stores -> here):
-// 8 x 3 x 151936 19.0 -> 19.4 (DCA_MEDIUM 21.4), 12 x 5 x 128256 30.6 -> 30.5 (32.5), 64 x 3 x 151936 67.9 -> 64.0
-// (DCA_SMALL 68.1), 100 x 3 x 50257 58.9 -> 43.1 (45.7), 500 x 3 x 50257 331 -> 186, 1024 x 3 x 151936 1072 -> 886.
+// kDcaIds ids of one row per block, 16 bytes per load and store where every row is aligned to them (VEC), else
+// one id each.
+//  DCA_MEDIUM, DCA_STREAM: nch blocks per row, neighbouring blocks on neighbouring ids, all loads of a thread
+// issued before the first exponential.  A row past the first rejection has coefficient 0: its gradient is
+// written without reading its logits (a quarter of the rows with accepted lengths uniform in 0..3).
+//  DCA_SMALL: the logits of every row are loaded, not behind the load of the row's coefficient, by a grid of
+// rows x nch, the row statistics' order: with rows a multiple of eight a row's logits are in the L2 of the
+// XCD that reads them.  There a thread's 16-byte loads and stores alternate.
+// Whole loss, us (cycles x positions x ids; every size row by row, in scalars off 16 bytes, -> here):
+// 8 x 3 x 151936 19.0 -> 18.9 (DCA_MEDIUM 21.4), 16 x 4 x 128256 28.8 -> 29.3 (all loads first 30.1), 64 x 3 x 151936
+// 67.9 -> 64.0 (DCA_SMALL 68.1), 100 x 3 x 50257 58.7 -> 42.8 (45.7), 500 x 3 x 50257 332 -> 187, 1024 x 3 x 151936
+// 1069 -> 882.
 template <bool VEC, int MODE>
 __global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch, const float *__restrict__ z,
                                                        const DcaRow *__restrict__ rows,
@@ -139,43 +139,47 @@ __global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch,
   int own_id = -1;
   if (want && (int)threadIdx.x < topk) own_id = rec_ids[r * topk + threadIdx.x];
   constexpr int kVec = kDcaIds / (4 * 256);
-  float v[kVec][4];
-#pragma unroll
-  for (int u = 0; u < kVec; ++u) {
+  auto load = [&](int u, float (&v)[4]) {
     if constexpr (VEC) {
       const int x = lo + 4 * ((int)threadIdx.x + 256 * u);
       const floatx4_t f = want && x < hi ? *reinterpret_cast<const floatx4_t *>(zr + x) : floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[u][q] = f[q];
+      for (int q = 0; q < 4; ++q) v[q] = f[q];
     } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int x = lo + (int)threadIdx.x + 256 * (4 * u + q);
-        v[u][q] = want && x < hi ? zr[x] : 0.f;
+        v[q] = want && x < hi ? zr[x] : 0.f;
       }
     }
+  };
+  constexpr bool kAhead = !(VEC && MODE == DCA_SMALL);
+  float v[kAhead ? kVec : 1][4];
+  if constexpr (kAhead) {
+#pragma unroll
+    for (int u = 0; u < kVec; ++u) load(u, v[u]);
   }
   const DcaRow d = rows[r];
   const float coef = (float)d.coef, M = (float)d.M, inv_s = (float)d.inv_s;
   const float rest = (float)((double)d.g_rest - d.gbar);
   const bool zero = d.coef == 0.0;
-  if (zero || own_id < lo || own_id >= hi) own_id = -1;
   float own_z = 0.f;
   int own_flag = 0;
-  if (own_id >= 0) {
+  auto load_own = [&]() {
+    if (zero || own_id < lo || own_id >= hi) own_id = -1;
+    if (own_id < 0) return;
     own_z = zr[own_id];
     own_flag = flags[r * topk + threadIdx.x];
-  }
-#pragma unroll
-  for (int u = 0; u < kVec; ++u) {
+  };
+  auto store = [&](int u, const float (&w)[4]) {
     floatx4_t o = {0.f, 0.f, 0.f, 0.f};
     if (!zero) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) o[q] = coef * (expf(v[u][q] - M) * inv_s) * rest;
+      for (int q = 0; q < 4; ++q) o[q] = coef * (expf(w[q] - M) * inv_s) * rest;
     }
     if constexpr (VEC) {
       const int x = lo + 4 * ((int)threadIdx.x + 256 * u);
-      if (x >= hi) continue;
+      if (x >= hi) return;
       if (MODE == DCA_STREAM) __builtin_nontemporal_store(o, reinterpret_cast<floatx4_t *>(gr + x));
       else *reinterpret_cast<floatx4_t *>(gr + x) = o;
     } else {
@@ -185,10 +189,24 @@ __global__ __launch_bounds__(256) void dca_grad_kernel(int V, int topk, int nch,
         if (x < hi) gr[x] = o[q];
       }
     }
+  };
+  if constexpr (kAhead) {
+    load_own();
+#pragma unroll
+    for (int u = 0; u < kVec; ++u) store(u, v[u]);
+  } else {
+#pragma unroll 1
+    for (int u = 0; u < kVec; ++u) {
+      load(u, v[0]);
+      store(u, v[0]);
+    }
+    load_own();   // (behind the logits, which need not wait for the record's ids)
   }
-  // written over the rest's once the stores above are done
-  if (!__syncthreads_or(own_id >= 0)) return;
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // written over the rest's, behind the block's stores above; those past the caches are waited for
+  if (MODE == DCA_STREAM) {
+    if (!__syncthreads_or(own_id >= 0)) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
   __syncthreads();
   if (own_id >= 0) gr[own_id] = coef * (expf(own_z - M) * inv_s) * (float)((double)own_flag - d.gbar);
 }
