@@ -172,29 +172,39 @@ void launch_row_stats(const char *name, const float *logits, long row_stride, in
                      stat_chunks(V), out, submax);
 }
 
-// max, normaliser and lowest arg-max of a whole row from its chunk statistics (all loads of
-// up to 12 chunks, 196608 ids, issued before the first use: one round trip)
-__device__ __forceinline__ void combine_stats(const RowStat *st, int nch, double &M, double &S, int &am) {
-  constexpr int kBatch = 12;
+// max, normaliser and lowest arg-max of a row from at most kBatch chunk statistics, all loads issued
+// before the first use: one round trip
+template <int kBatch>
+__device__ __forceinline__ void combine_batch(const RowStat *st, int nch, float &m, double &s, int &a) {
+  uint4 v[kBatch];
+  const uint4 *src = reinterpret_cast<const uint4 *>(st);
+#pragma unroll
+  for (int c = 0; c < kBatch; ++c) v[c] = src[c < nch ? c : 0];
+#pragma unroll
+  for (int c = 0; c < kBatch; ++c) {
+    const float mc = __uint_as_float(v[c].x);
+    if (c < nch && mc > m) { m = mc; a = (int)v[c].y; }
+  }
+#pragma unroll
+  for (int c = 0; c < kBatch; ++c) {
+    if (c >= nch) continue;
+    const double sum = __longlong_as_double((long long)(((unsigned long long)v[c].w << 32) | v[c].z));
+    s += sum * exp((double)__uint_as_float(v[c].x) - (double)m);
+  }
+}
+
+// max, normaliser and lowest arg-max of a whole row from its nch chunk statistics; most: the largest nch
+// among the lanes of the wave.  Up to 12 chunks (196608 ids) take one round trip, up to 4 (65536 ids) a
+// shorter one (accepts, us, batches of twelve alone -> here: 6 sequences of 50257 ids, k = 4, 33.8 -> 33.5;
+// 2 of 32001 with their record 24.5 -> 24.1).
+__device__ __forceinline__ void combine_stats(const RowStat *st, int nch, int most, double &M, double &S, int &am) {
   float m = -INFINITY;
   int a = 0;
   double s = 0.0;
-  if (nch <= kBatch) {
-    uint4 v[kBatch];
-    const uint4 *src = reinterpret_cast<const uint4 *>(st);
-#pragma unroll
-    for (int c = 0; c < kBatch; ++c) v[c] = src[c < nch ? c : 0];
-#pragma unroll
-    for (int c = 0; c < kBatch; ++c) {
-      const float mc = __uint_as_float(v[c].x);
-      if (c < nch && mc > m) { m = mc; a = (int)v[c].y; }
-    }
-#pragma unroll
-    for (int c = 0; c < kBatch; ++c) {
-      if (c >= nch) continue;
-      const double sum = __longlong_as_double((long long)(((unsigned long long)v[c].w << 32) | v[c].z));
-      s += sum * exp((double)__uint_as_float(v[c].x) - (double)m);
-    }
+  if (most <= 4) {
+    combine_batch<4>(st, nch, m, s, a);
+  } else if (most <= 12) {
+    combine_batch<12>(st, nch, m, s, a);
   } else {
     for (int c = 0; c < nch; ++c)
       if (st[c].max > m) { m = st[c].max; a = st[c].argmax; }
@@ -270,7 +280,7 @@ __global__ __launch_bounds__(64) void accept_decide_kernel(int B, int k, int V, 
   int nid = 0x7fffffff;
   if (is_t || is_d) {
     const RowStat *st = is_t ? tstat + (long)(b * k1 + lane) * nch : dstat + (long)(b * k + lane - k1) * nch_d;
-    combine_stats(st, is_t ? nch : nch_d, M, S, am);
+    combine_stats(st, is_t ? nch : nch_d, max(nch, nch_d), M, S, am);
     if (tnuc && mode != GM_GREEDY) {   // top-p: p and q are the rows' nuclei
       const NucRow nr = is_t ? tnuc[b * k1 + lane] : dnuc[b * k + lane - k1];
       M = nr.m;
@@ -424,7 +434,7 @@ __global__ __launch_bounds__(1024) void record_topk_kernel(int k, int V, float i
   if (tid == (int)blockDim.x - 1) {   // (the last wave: the first ones have more to do before the barrier)
     double M, S;
     int am;
-    combine_stats(tstat + row * nch, nch, M, S, am);
+    combine_stats(tstat + row * nch, nch, nch, M, S, am);
     sh_M = M;
     sh_lse = log(S);
     sh_cnt = 0;
@@ -1080,8 +1090,9 @@ __global__ __launch_bounds__(kNucThreads) void nucleus_kernel(int V, double inv_
     if (queued && qn <= (unsigned)kNucRank) {
       // few: each id's running mass is the mass of the ids ranked before it; the boundary is the
       // id whose own mass takes it to thr, and the ids of equal logit past it are left out.  The
-      // ids before thr are the whole nucleus, so a draw from it is made here: their weights (the
-      // terms the scan over the vocabulary would take) in id order, summed by one thread.
+      // ids before thr are the whole nucleus, so a draw from it is made here: their weights in id
+      // order, summed by one thread.  (The float32 terms of the scan over the vocabulary without its
+      // common factor 1 / s, which it sums as a tree: the sums agree but for float64 rounding.)
       unsigned long long *qm = hist;
       for (unsigned i = tid; i < qn; i += kNucThreads) qm[i] = nuc_mass(qv[i], inv_td, m, etab);
       if (tid == 0) sh_bin = 0;
